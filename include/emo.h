@@ -120,7 +120,9 @@ typedef struct {
                                      specialised to the graph (emo_eval_intervals; 0 there
                                      means the interpreting kernel), 8 two-pass chain scan
                                      whose window copies and slack stores follow per-thread
-                                     plans fixed for the call (chain_scan_full) */
+                                     plans fixed for the call (chain_scan_full), 9 one-kernel
+                                     policy search (emo_dp_search; another kind there is the
+                                     evaluator of a search by stages) */
     int32_t chain_lanes;          /* lanes per candidate of the chain-lane kernels, 0 when the
                                      candidate-dependent nodes do not form at most 64 disjoint
                                      chains */
@@ -391,8 +393,12 @@ emo_status emo_graph_set_timing_events(emo_graph_t g, void *begin_event, void *e
  *   result           device emo_selection, 8-byte aligned: index = floor(makespan / quantum) of
  *                    the policy found, or -1 (energy and makespan NaN) when no policy meets
  *                    the target; num_feasible = the policies stored after the last stage.
- * One call runs P + 1 evaluations of at most max_states x F candidates each, asynchronously on
- * `stream`.  Not to be called concurrently with itself on the same graph.
+ * Asynchronous on `stream`.  A search by stages runs P + 1 evaluations of at most max_states x F
+ * candidates each.  When the packs are set in the order the evaluators visit them (pack_order NULL or
+ * the identity, and pack_order_monotone 1), exact_time_sums is 1 and the buckets fit one workgroup
+ * (buckets x F at most 16,384, and the stored policies' live finish times in its LDS), one kernel runs
+ * all stages with the same results bit for bit and 4 bytes x buckets x P of scratch; interpreted mode
+ * always searches by stages.  Not to be called concurrently with itself on the same graph.
  */
 emo_status emo_dp_search(emo_graph_t g, float latency_target, float quantum, const int32_t *pack_order,
                          int32_t max_states, uint8_t *best_levels, emo_selection *result, void *stream);

@@ -245,6 +245,8 @@ struct emo_graph_s {
     std::vector<char> dyn;                   // depends on the candidate
     std::vector<float> const_eft;            // finish time of candidate-independent nodes
     std::vector<float> tmin;                 // each pack's least time over its levels
+    std::vector<float> ttop, etop;           // each pack's time and energy at level F-1
+    std::vector<float> emin, emax;           // each pack's least and largest energy
     float t_const = 0.f;
     emo_graph_info info{};
     std::vector<void *> allocations;         // device memory owned by the handle
@@ -280,6 +282,10 @@ struct emo_graph_s {
     Arena arena;                             // per-call scratch, kept between calls
     Arena dp_arena;                          // scratch of the policy search (whose evaluations
                                              // use `arena`)
+    // one-kernel policy search, built on first use under dp_arena.mu: [1] with the energy blocks of
+    // the cut-segment kernels, [0] with those of every other program-order kind
+    int search_state[2] = {0, 0};            // 0 not tried, 1 ready, -1 does not apply
+    emo::SearchProg search[2];
     // profiling hook (hipEvent_t handles owned by the caller)
     hipEvent_t ev_begin = nullptr;
     hipEvent_t ev_end = nullptr;
@@ -1178,6 +1184,17 @@ emo_status emo_load_graph(int32_t num_nodes, int32_t num_edges, const int32_t *e
         for (int32_t f = 1; f < F; ++f) m = std::min(m, pack_time[static_cast<size_t>(p) * F + f]);
         g->tmin[p] = m;
     }
+    g->ttop.resize(P);
+    g->etop.resize(P);
+    g->emin.resize(P);
+    g->emax.resize(P);
+    for (int32_t p = 0; p < P; ++p) {
+        const float *e = pack_energy + static_cast<size_t>(p) * F;
+        g->ttop[p] = pack_time[static_cast<size_t>(p) * F + F - 1];
+        g->etop[p] = e[F - 1];
+        g->emin[p] = *std::min_element(e, e + F);
+        g->emax[p] = *std::max_element(e, e + F);
+    }
     for (int32_t v = 0; v < V; ++v)
         if (g->pack[v] >= 0) g->dur[v] = 0.f;
     // merge duplicate edges
@@ -1724,6 +1741,72 @@ struct DPBuffers {
     float *Tst, *T, *E;
 };
 
+// Whether a search that sets the packs in `order` can run as one kernel over NB buckets, with the
+// makespans and energies of the kernels that would evaluate its candidates, bit for bit; then *prog is
+// its program, built on the first such search.  That needs:
+//   - packs set in the order the kernels visit them (increasing id), so that a stored policy is its
+//     live finish times and everything after the stage's pack runs at the top level;
+//   - exact time sums (precomputed path tails then give the recurrence's makespan);
+//   - evaluating kernels that sum energies in program order: every kind but the chain kernels, with
+//     blocks of 64 packs (counted from each segment's start in the cut-segment kernels).
+// Interpreted mode keeps the search by stages.  With g->dp_arena.mu held.
+bool search_in_one_kernel(emo_graph_s *g, const std::vector<int32_t> &order, int64_t NB, const emo::SearchProg **prog) {
+    if (g->kernel_mode == EMO_KERNELS_INTERPRETED || NB < 1 || g->P < 1) return false;
+    if (!g->info.exact_time_sums || !g->jg.pack_monotone) return false;
+    for (int32_t i = 0; i < g->P; ++i)
+        if (order[i] != i) return false;
+    const bool one_or_chain = g->jit_eligible || g->chain_eval;
+    if (g->chains.lanes > 0 && !one_or_chain) return false;
+    bool cut = false;
+    if (g->cut_ok && !(g->jit_eligible && !g->chain_eval)) {
+        std::lock_guard<std::mutex> lock(g->jit_mu);
+        cut = g->cut_state != -1;
+    }
+    const int v = cut ? 1 : 0;
+    if (g->search_state[v] == 0) {
+        g->search_state[v] = -1;
+        try {
+            std::vector<int32_t> ends;
+            int32_t pack = 0, seg = 0, in_block = 0;
+            for (size_t i = 0; i < g->jg.ops.size(); ++i) {
+                if (cut && static_cast<int32_t>(i) == g->cut_plan.seg[seg + 1]) {
+                    ++seg;
+                    if (in_block) ends.push_back(pack - 1);
+                    in_block = 0;
+                }
+                if (g->jg.ops[i].pack < 0) continue;
+                ++pack;
+                if (++in_block == emo::kEnergyBlock) {
+                    ends.push_back(pack - 1);
+                    in_block = 0;
+                }
+            }
+            if (in_block) ends.push_back(pack - 1);
+            const emo::SearchHost h = emo::search_build(g->jg, g->ttop, g->etop, g->emin, g->emax, ends);
+            if (h.L >= 0) {
+                emo::SearchProg sp;
+                sp.P = g->P;
+                sp.F = g->F;
+                sp.L = h.L;
+                sp.rec_words = h.rec_words;
+                sp.t_const = g->t_const;
+                sp.static_power = g->static_power;
+                if (upload(*g, h.recs, &sp.recs) == EMO_OK && upload(*g, h.fix, &sp.fix) == EMO_OK &&
+                    upload(*g, h.etop, &sp.etop) == EMO_OK) {
+                    g->search[v] = sp;
+                    g->search_state[v] = 1;
+                } else {
+                    (void)hipGetLastError();
+                }
+            }
+        } catch (const std::bad_alloc &) {   // the search by stages needs none of this
+        }
+    }
+    if (g->search_state[v] != 1) return false;
+    *prog = &g->search[v];
+    return emo::search_fits(g->F, g->search[v].L, NB);
+}
+
 size_t dp_layout(int64_t S, int64_t R, int32_t P, DPBuffers *b, char *base) {
     size_t off = 0;
     auto take = [&](size_t bytes) {
@@ -1787,13 +1870,25 @@ emo_status emo_dp_search(emo_graph_t g, float latency_target, float quantum, con
     hipStream_t st = static_cast<hipStream_t>(stream);
     DeviceGuard guard(g->device);
     DPBuffers b{};
-    const size_t bytes = dp_layout(S, R, P, &b, nullptr);
     std::lock_guard<std::mutex> lock(g->dp_arena.mu);
+    const emo::SearchProg *prog = nullptr;
+    const bool one = search_in_one_kernel(g, order, NB, &prog);
+    const size_t bytes = one ? static_cast<size_t>(P) * static_cast<size_t>(NB) * sizeof(uint32_t)
+                             : dp_layout(S, R, P, &b, nullptr);
     void *base = nullptr;
     hipError_t e = arena_acquire(g->dp_arena, bytes, st, &base);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         return fail(EMO_ERR_OUT_OF_MEMORY, "scratch of %zu bytes: %s", bytes, hipGetErrorString(e));
+    }
+    if (one) {
+        g->info.last_kernels = 9;
+        if (g->ev_begin) e = hipEventRecord(g->ev_begin, st);
+        if (e == hipSuccess) e = emo::launch_search(*prog, g->dg.tab, latency_target, q, bmin, NB, base, best_levels, result, st);
+        if (e == hipSuccess && g->ev_end) e = hipEventRecord(g->ev_end, st);
+        hipError_t er = arena_release(g->dp_arena, st);
+        if (e == hipSuccess) e = er;
+        return after_launch(e, "emo_dp_search");
     }
     dp_layout(S, R, P, &b, static_cast<char *>(base));
     // dp[0] = {P_0}, expanded into the first stage's candidates (row buffer 1 holds P_0)

@@ -259,6 +259,36 @@ struct JitGraph {
     std::vector<JitOp> ops;
 };
 
+// One-kernel policy search (emo_search.hip): packs set in visiting order, exact time sums.  The
+// stages' records and the fixed nodes after their packs (kRec*, kFix* words), and the packs' energies
+// at the top level by energy block.
+constexpr int kSearchMaxLive = 64;     // finish times kept per stored policy at most
+struct SearchHost {
+    int L = -1;                        // live finish times per policy (4, 8, 16, 32 or 64), or -1
+    int rec_words = 0;
+    std::vector<uint32_t> recs, fix;
+    std::vector<float> etop;
+};
+struct SearchProg {
+    int32_t P = 0, F = 1, L = 0, rec_words = 0;
+    float t_const = 0.f, static_power = 0.f;
+    const uint32_t *recs = nullptr;    // [P][rec_words]
+    const uint32_t *fix = nullptr;
+    const float *etop = nullptr;       // [energy blocks + 2][kEnergyBlock], zero past a block's end
+};
+// ttop, etop: each pack's time and energy at the top level; emin, emax: its least and largest energy;
+// blk_end: the last pack of each energy block of the evaluators, in increasing order.  Needs packs
+// visited in increasing id.  L stays -1 when the kernel does not apply (too many live finish times, or
+// energies whose fp64 sums could round).
+SearchHost search_build(const JitGraph &g, const std::vector<float> &ttop, const std::vector<float> &etop,
+                        const std::vector<float> &emin, const std::vector<float> &emax,
+                        const std::vector<int32_t> &blk_end);
+// Whether NB buckets fit the kernel (its LDS, its record prefetch) and suit one workgroup.
+bool search_fits(int F, int L, int64_t NB);
+// The search over NB >= 1 buckets and P >= 1 packs.  scratch: P * NB back pointers (uint32).
+hipError_t launch_search(const SearchProg &g, const float2 *tab, float tmax, double q, int64_t bmin, int64_t NB,
+                         void *scratch, uint8_t *best, emo_selection *res, hipStream_t s);
+
 // Level words are read a line at a time only when packs are visited in increasing id; in any
 // other order a word would stay live from its first to its last use (register pressure), so each
 // level byte is then loaded on its own.

@@ -158,3 +158,57 @@ def test_dp_on_workload_tables(torch, emo, k):
     assert abs(sel.energy - r.energy) <= 1e-5 * r.energy, (sel.energy, r.energy)
     assert sel.index == math.floor(sel.makespan / float(np.float32(q)))
     print(f"  energy {sel.energy} vs oracle {r.energy}; states {sel.num_feasible} vs {r.num_states}", flush=True)
+
+
+def _search_graph(kind):
+    rng = np.random.default_rng(77)
+    if kind == "training":                       # one-kernel evaluators, 512 packs
+        return synth.config_graph(3)
+    if kind == "odd-blocks":                     # a last energy block of 3 packs, 11 levels
+        return synth.packed_graph(5, 131, 3, 11, sync_every=50)
+    if kind == "segmented":                      # a table past one kernel's LDS, no cuts
+        return synth.without_cuts(synth.packed_graph(6, 640, 4, 16))
+    if kind == "cuts":                           # cut-segment evaluators, whole energy blocks
+        return synth.packed_graph(7, 768, 3, 16)
+    if kind == "cuts-ragged":                    # segments of 160 packs: blocks of 64, 64 and 32
+        return dyadic(synth.packed_graph(8, 960, 5, 16, sync_every=160), rng)
+    if kind == "one-level":
+        return synth.packed_graph(9, 70, 2, 1)
+    if kind == "wide-levels":
+        return synth.stream_graph(10, 40, 2, 256)
+    # fixed nodes between packs, several predecessors, nodes without successors
+    return dyadic(synth.random_dag(rng, 60, 0.08, 0.6, 5, shuffle_ids=False, shuffle_packs=False), rng)
+
+
+@pytest.mark.parametrize("kind", ["training", "odd-blocks", "segmented", "cuts", "cuts-ragged", "one-level",
+                                  "wide-levels", "fixed-nodes"])
+def test_dp_one_kernel_matches_stages(torch, emo, kind):
+    """The one-kernel search (packs in visiting order, exact time sums) gives the search by stages
+    (interpreted mode) bit for bit: levels, energy, makespan, bucket and state count, from one bucket
+    to as many as one workgroup takes, including no feasible policy; past that, and off the grid or in
+    another order, the search by stages runs."""
+    g = _search_graph(kind)
+    P, F = g.num_packs, g.num_levels
+    ga, gi = emo.EmoGraph(g, device=0), emo.EmoGraph(g, device=0, kernel_mode=emo.KERNELS_INTERPRETED)
+    T0 = float(dp.eval_batch(g, np.full((1, P), F - 1, np.uint8))[0][0])
+    cases = [(1.05, 64), (1.0, 1), (1.3, 3), (0.5, 8), (1.02, 200 if F <= 16 else 20)]
+    if kind == "training":   # (the fixed-node graph's 5 levels would pass the LDS limit first)
+        cases += [(1.1, 16384 // F - 3), (1.1, 16384 // F + 40)]
+    for ratio, nb in cases:
+        tgt = float(np.float32(ratio * T0))
+        q = float(np.float32(max(abs(ratio - 1.0), 0.01) * T0 / nb))
+        print(f"[case] dp one kernel {kind} P={P} F={F} target={tgt} buckets~{nb}", flush=True)
+        kw = dict(max_states=1 << 16)
+        a, sa = run(emo, ga, tgt, q, **kw)
+        one = ga.info()["last_kernels"] == 9
+        b, sb = run(emo, gi, tgt, q, **kw)
+        assert gi.info()["last_kernels"] == 0
+        assert (sa.index, sa.num_feasible) == (sb.index, sb.num_feasible), (sa, sb)
+        if sa.index >= 0:
+            assert np.array_equal(a, b) and (sa.energy, sa.makespan) == (sb.energy, sb.makespan), (sa, sb)
+        assert one == (ratio > 0.9 and nb * F < 16384), (ratio, nb, one)
+    ga.dp_search(float(np.float32(1.05 * T0)), T0, np.arange(P)[::-1].copy())
+    assert P == 1 or ga.info()["last_kernels"] != 9
+    off = emo.EmoGraph(synth.scaled_times(g, 1.1), device=0)
+    off.dp_search(float(np.float32(1.2 * T0)), T0)
+    assert off.info()["last_kernels"] != 9
