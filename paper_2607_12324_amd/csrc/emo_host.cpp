@@ -90,6 +90,7 @@ constexpr int32_t kHotSpan = 96;
 
 constexpr int32_t kJitMaxOps = 2048;      // larger graphs compile too slowly as one kernel
 constexpr int32_t kJitMaxSlackOps = 160;  // every finish time stays in a VGPR
+constexpr int32_t kJitMaxNodes = 1024;    // per-node slack in one kernel: columns
 // Segmented kernels (larger graphs): steps per segment kernel and per recompute sub-segment,
 // and the largest graph compiled this way (compile time grows with the step count).
 constexpr int32_t kChainSegOps = 256;
@@ -261,6 +262,10 @@ struct emo_graph_s {
     int jit_state = 0;                       // 0 not tried, 1 compiled, -1 failed
     emo::JitModule jm;
     std::string jit_log;
+    // slack of every node in one specialised kernel (jg.nodes not empty)
+    int node_state = 0;                      // 0 not tried, 1 compiled, -1 failed
+    emo::JitModule jn;
+    bool nodes_are_packs = false;            // node v is pack v for every node: per-node = per-pack
     // segmented kernels: forward kernels for eval/select when one kernel would not hold the
     // table in LDS, backward kernels for slack when the graph is too large to keep every finish
     // time
@@ -624,6 +629,7 @@ void release_device(emo_graph_s *g) {
     if (g->device >= 0) {
         DeviceGuard guard(g->device);
         emo::jit_unload(&g->jm);
+        emo::jit_unload(&g->jn);
         emo::jit_unload(&g->jc);
         emo::jit_unload(&g->jk);
         for (void *p : g->allocations) (void)hipFree(p);
@@ -823,6 +829,25 @@ emo::JitGraph make_jit_graph(const emo_graph_s &g, const Schedule &sc) {
     return jg;
 }
 
+// Every node in id order for the per-node slack kernel, when each edge leads to a higher id (the
+// kernel walks ids downwards, so that its slack leaves in whole pieces of a row).
+void fill_jit_nodes(emo_graph_s &g, const Schedule &sf) {
+    for (int32_t u = 0; u < g.V; ++u)
+        for (int32_t k = g.succ_off[u]; k < g.succ_off[u + 1]; ++k)
+            if (g.succ[k] <= u) return;
+    std::vector<int32_t> step(g.V, -1);
+    for (size_t i = 0; i < sf.seq.size(); ++i) step[sf.seq[i]] = static_cast<int32_t>(i);
+    g.jg.nodes.resize(g.V);
+    for (int32_t v = 0; v < g.V; ++v) {
+        emo::JitNode &nd = g.jg.nodes[v];
+        nd.step = step[v];
+        nd.eft = g.const_eft[v];
+        nd.dur = g.pack[v] >= 0 ? 0.f : g.dur[v];
+        nd.has_in = g.pred_off[v + 1] > g.pred_off[v];
+        nd.out.assign(g.succ.begin() + g.succ_off[v], g.succ.begin() + g.succ_off[v + 1]);
+    }
+}
+
 // Steps that are cut nodes: nodes that every other node precedes or follows.  At position i of
 // a topological order that holds exactly when no edge jumps over position i, no node before it
 // is a sink and no node after it is a source.  Returns their step indices in increasing order.
@@ -907,7 +932,15 @@ std::string jit_source(const emo_graph_s &g, int *block_out) {
     // one LDS copy of a large table serves a larger workgroup
     const int block = !tab_lds || tb <= 16 * 1024 ? 256 : (tb <= 32 * 1024 ? 512 : 1024);
     *block_out = block;
-    return emo::jit_generate(g.jg, with_slack, tab_lds, block);
+    return emo::jit_generate(g.jg, with_slack ? emo::JitSlack::kPacks : emo::JitSlack::kNone, tab_lds, block);
+}
+
+// Source of the per-node slack kernel (g.jg.nodes not empty: its table is at most 160 packs' rows).
+std::string node_source(const emo_graph_s &g, int *block_out) {
+    const size_t tb = jit_table_bytes(g);
+    const bool tab_lds = tb <= kJitTableLdsSlack;
+    *block_out = !tab_lds || tb <= 16 * 1024 ? 256 : 512;
+    return emo::jit_generate(g.jg, emo::JitSlack::kNodes, tab_lds, *block_out);
 }
 
 // Generates and compiles the time-interval kernels once; returns 1 when they are ready.
@@ -985,6 +1018,29 @@ int ensure_jit(emo_graph_s *g) {
     return 1;
 }
 
+// Generates and compiles the per-node slack kernel once; returns 1 when it is ready.
+int ensure_nodes(emo_graph_s *g) {
+    std::lock_guard<std::mutex> lock(g->jit_mu);
+    if (g->node_state != 0) return g->node_state;
+    int block = 256;
+    const std::string src = node_source(*g, &block);
+    DeviceGuard guard(g->device);
+    emo::JitModule m;
+    std::string log;
+    if (emo::jit_compile_nodes(src, &m, &log) != 0) {
+        g->jit_log = log;
+        g->node_state = -1;
+        g->info.specialized |= 4;
+        return -1;
+    }
+    m.block = block;
+    if (jit_table_bytes(*g) > 16 * 1024) emo::jit_set_caps(&m);
+    g->jn = m;
+    g->node_state = 1;
+    g->info.compile_seconds += static_cast<float>(m.compile_seconds);
+    return 1;
+}
+
 emo::ChainPlan chain_plan(const emo_graph_s &g) {
     return emo::jit_chain_plan(g.jg, g.chain_slack, kChainSegOps, kChainSubOps);
 }
@@ -1035,8 +1091,8 @@ int ensure_cut(emo_graph_s *g) {
 bool aligned(const void *p, size_t a) { return reinterpret_cast<uintptr_t>(p) % a == 0; }
 
 // Which kernels a batch call uses (the value of emo_graph_info.last_kernels, except that the
-// windowed form of the chain lanes reports 4).
-enum class Path { kInterpreted = 0, kSingle = 1, kChain = 2, kChainLanes = 3, kCut = 5 };
+// windowed form of the chain lanes reports 4 and the per-node slack kernel 1).
+enum class Path { kInterpreted = 0, kSingle = 1, kChain = 2, kChainLanes = 3, kCut = 5, kNodes = 10 };
 
 // Chooses the kernels of a batch call, compiling specialised kernels on first use.  Returns
 // EMO_OK and sets *path, or an error in EMO_KERNELS_SPECIALIZED mode.
@@ -1044,7 +1100,20 @@ emo_status choose_path(emo_graph_s *g, const uint8_t *levels, const float *slack
                        int64_t B, Path *path) {
     *path = Path::kInterpreted;
     if (g->kernel_mode == EMO_KERNELS_INTERPRETED) return EMO_OK;
-    if (slack && per_node) return EMO_OK;   // per-node slack: interpreted kernels only
+    if (slack && per_node) {
+        // one kernel specialised to the graph, else the interpreting kernels
+        const bool wide_stores = !g->jg.nodes.empty() && g->V % 16 == 0;
+        if (g->jg.nodes.empty() || !aligned(levels, static_cast<size_t>(emo::jit_level_width(g->jg))) ||
+            (wide_stores && !aligned(slack, 16)))
+            return EMO_OK;
+        if (ensure_nodes(g) == 1) {
+            *path = Path::kNodes;
+            return EMO_OK;
+        }
+        if (g->kernel_mode == EMO_KERNELS_SPECIALIZED)
+            return fail(EMO_ERR_DEVICE, "per-node slack kernel failed to compile: %.400s", g->jit_log.c_str());
+        return EMO_OK;
+    }
     if (slack && g->chain_scan_first && !g->jit_slack_eligible &&
         emo::chains_windowed_ok(g->chains, levels, slack)) {
         *path = Path::kChainLanes;
@@ -1249,6 +1318,9 @@ emo_status emo_load_graph(int32_t num_nodes, int32_t num_edges, const int32_t *e
     g->jit_eligible = nops >= 1 && nops <= kJitMaxOps;
     g->jit_slack_eligible = g->jit_eligible && nops <= kJitMaxSlackOps;
     g->jit_slack_staged = sf.monotone && P % 16 == 0;
+    if (g->jit_slack_eligible && sf.monotone && V <= kJitMaxNodes) fill_jit_nodes(*g, sf);
+    g->nodes_are_packs = V == P;
+    for (int32_t v = 0; v < V && g->nodes_are_packs; ++v) g->nodes_are_packs = g->pack[v] == v;
     const bool narrow = pe.n_hot + pe.n_cold <= kChainMaxLive;
     // Without slack, one kernel past kJitTableLds reads the table from global memory: the
     // segmented kernels (table windows in LDS) are then faster whenever the live set allows.  At
@@ -1448,11 +1520,17 @@ emo_status evaluate(emo_graph_t g, const uint8_t *levels, int64_t B, float *make
     }
     if (!makespan && !energy && !slack && !tg.n) return ok();
     if (!levels && g->P > 0) return fail(EMO_ERR_INVALID_ARGUMENT, "levels is NULL");
+    // every node is the pack of its id: the two slack layouts are the same, and so are the values of
+    // the kinds that follow the recurrence and sum energies in program order
+    if (per_node && slack && g->nodes_are_packs && g->kernel_mode != EMO_KERNELS_INTERPRETED &&
+        (g->jit_slack_eligible || (g->chains.lanes == 0 && (g->info.exact_time_sums || !g->cut_ok))))
+        per_node = 0;
     Path path = Path::kInterpreted;
     if ((s = choose_path(g, levels, slack, per_node != 0, B, &path)) != EMO_OK) return s;
     DeviceGuard guard(g->device);
     // one selection partial record per block of the evaluating kernel
     const int64_t nblocks = path == Path::kSingle  ? emo::jit_blocks(g->jm, B)
+                            : path == Path::kNodes ? emo::jit_blocks(g->jn, B)
                             : path == Path::kChain ? emo::jit_chain_blocks(g->jc, B)
                             : path == Path::kCut   ? emo::jit_cut_blocks(g->jk, B)
                             : path == Path::kChainLanes ? emo::select_results_blocks(B)
@@ -1485,6 +1563,7 @@ emo_status evaluate(emo_graph_t g, const uint8_t *levels, int64_t B, float *make
                                ? 6
                                : path == Path::kChainLanes && emo::chains_windowed_ok(g->chains, levels, slack)
                                      ? 4
+                               : path == Path::kNodes ? 1
                                      : static_cast<int32_t>(path);
     hipError_t e = g->ev_begin ? hipEventRecord(g->ev_begin, st) : hipSuccess;
     if (e == hipSuccess) {
@@ -1496,8 +1575,8 @@ emo_status evaluate(emo_graph_t g, const uint8_t *levels, int64_t B, float *make
         } else if (path == Path::kChainLanes) {
             e = emo::launch_chains(g->dg, g->chains, levels, B, makespan, energy, slack, tg, work, st);
         } else if (slack) {
-            if (path == Path::kSingle) {
-                e = emo::jit_launch_slack(g->jm, levels, B, g->dg.tab, slack, makespan, energy, tg, st);
+            if (path == Path::kSingle || path == Path::kNodes) {
+                e = emo::jit_launch_slack(path == Path::kNodes ? g->jn : g->jm, levels, B, g->dg.tab, slack, makespan, energy, tg, st);
             } else {
                 e = emo::launch_slack(g->dg, prog, per_node ? g->V : g->P, levels, B, slack,
                                       makespan, energy, tg, work, st);

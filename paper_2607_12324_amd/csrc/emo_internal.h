@@ -251,12 +251,24 @@ struct JitOp {
     std::vector<int32_t> out;      // steps of successors (all candidate-dependent)
 };
 
+// One node of the graph by id (for the slack of every node).
+struct JitNode {
+    int32_t step;                  // its step, or -1 for a candidate-independent node
+    float eft;                     // that node's finish time
+    float dur;                     // fixed duration (0 for a pack)
+    bool has_in;                   // some node precedes it
+    std::vector<int32_t> out;      // ids of its successors
+};
+
 struct JitGraph {
     int32_t P = 0, F = 1;
     float static_power = 0.f;
     float t_const = 0.f;
     bool pack_monotone = true;
     std::vector<JitOp> ops;
+    // every node in id order, when each edge leads to a higher id and the graph is small enough for
+    // the per-node slack kernel (else empty)
+    std::vector<JitNode> nodes;
 };
 
 // One-kernel policy search (emo_search.hip): packs set in visiting order, exact time sums.  The
@@ -382,7 +394,11 @@ struct JitModule {
 
 // Bytes per level load in generated kernels (16, 4 or 1): the alignment they need.
 
-std::string jit_generate(const JitGraph &g, bool with_slack, bool tab_lds, int block);
+// The one-kernel module: emo_sp_select and, with kPacks, emo_sp_slack; with kNodes emo_sp_nodes alone
+// (the slack of every node, JitGraph.nodes).
+enum class JitSlack { kNone, kPacks, kNodes };
+std::string jit_generate(const JitGraph &g, JitSlack slack, bool tab_lds, int block);
+int jit_compile_nodes(const std::string &src, JitModule *out, std::string *log);   // out->slack
 // Segments of about seg_ops steps (cut where the pack steps so far are a multiple of 64) and
 // recompute sub-segments of at most sub_ops steps.
 ChainPlan jit_chain_plan(const JitGraph &g, bool with_slack, int seg_ops, int sub_ops);

@@ -365,10 +365,15 @@ LevelPlan emit_forward(std::ostringstream &o, const JitGraph &g, std::vector<std
     return lp;
 }
 
-// Slack output staging: packs [p0, p0 + kc) of the wave's 64 candidates are collected in LDS
-// as stg[pack - p0][lane] (row stride 65 floats, conflict-free writes) and written with 16-byte
-// stores; with kc = 32 each candidate's segment is one whole 128-byte line.
-int stage_chunk(int P) { return P % 32 == 0 ? 32 : 16; }
+// Slack output staging: columns [p0, p0 + kc) of the wave's 64 candidates are collected in LDS
+// as stg[column - p0][lane] (row stride 65 floats, conflict-free writes) and written a row piece at a
+// time; with kc = 32 each candidate's piece is one 128-byte line.  The last piece of a row may be
+// shorter, and rows of any column count are staged: a lane that stores its own row a float at a time
+// spreads each store over 64 rows (2^19 candidates: 24 packs 54 us that way and 14 staged, 35 packs 80
+// and 31, 100 packs 233 and 61).
+int stage_chunk(int cols) { return cols >= 32 ? 32 : (cols + 3) / 4 * 4; }
+// 16-byte stores when rows keep that alignment, else a float per lane.
+bool stage_vec(int cols) { return cols % 4 == 0; }
 
 // Backward pass for per-pack slack (requires the forward's f<i>, T and the level words).
 // Pack durations are read from the table again at an index offset by a zero the compiler cannot
@@ -405,7 +410,8 @@ void emit_backward(std::ostringstream &o, const JitGraph &g, bool staged,
             const int kc = stage_chunk(g.P);
             if (staged) {
                 o << "  stg[" << (p % kc) * 65 << " + lane] = lf" << i << " - f" << i << ";\n";
-                if (p % kc == 0) o << "  emo_flush(stg, stg_bad, S, wbase, B, " << p << ");\n";
+                if (p % kc == 0)
+                    o << "  emo_flush(stg, stg_bad, S, wbase, B, " << p << ", " << std::min(kc, g.P - p) << ");\n";
             } else {
                 o << "  if (active) S[cand * " << g.P << "LL + " << p << "] = isbad ? __builtin_nanf(\"\") : lf"
                   << i << " - f" << i << ";\n";
@@ -414,19 +420,25 @@ void emit_backward(std::ostringstream &o, const JitGraph &g, bool staged,
     }
 }
 
-// Device routine that writes the slack of packs [p0, p0 + EMO_KC) of the wave's 64 candidates
-// from the LDS staging area (rows of P floats per candidate).
-std::string flush_source(int P) {
-    return std::string(R"(
-// Writes the slack of packs [p0, p0 + EMO_KC) of the wave's 64 candidates, staged in LDS.
+// Device routine that writes the slack of columns [p0, p0 + n) of the wave's 64 candidates from the
+// LDS staging area (rows of `cols` floats per candidate).  n is a constant at every call.  Callers
+// whose column count is a multiple of 16 pass a 16-byte aligned S.
+std::string flush_source(int cols) {
+    const bool vec = stage_vec(cols), either = vec && cols % 16 != 0;
+    const std::string row_of = "row * " + std::to_string(cols) + "LL + p0";
+    std::string s = R"(
+// Writes the slack of columns [p0, p0 + n) of the wave's 64 candidates, staged in LDS.
 __device__ __forceinline__ void emo_flush(float *stg, const unsigned int *stg_bad,
                                           float *__restrict__ S, long long wbase, long long B,
-                                          int p0) {
+                                          int p0, int n) {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   const int lane = threadIdx.x % EMO_WAVE;
-  constexpr int per_row = EMO_KC / 4;          // 16-byte pieces per candidate segment
+)";
+    if (either) s += "  if (((unsigned long long)S & 15u) == 0u) {\n";
+    if (vec)
+        s += R"(  constexpr int per_row = EMO_KC / 4;          // 16-byte pieces per candidate segment
 #pragma unroll
   for (int m = 0; m < per_row; ++m) {
     const int j = lane + EMO_WAVE * m;
@@ -438,13 +450,58 @@ __device__ __forceinline__ void emo_flush(float *stg, const unsigned int *stg_ba
     v.w = stg[(4 * part + 3) * 65 + r];
     if (stg_bad[r]) { v.x = EMO_NAN; v.y = EMO_NAN; v.z = EMO_NAN; v.w = EMO_NAN; }
     const long long row = wbase + r;
-    if (row < B) *(float4 *)(S + row * )" + std::to_string(P) + R"(LL + p0 + 4 * part) = v;
+    if (row < B && 4 * part < n) *(float4 *)(S + )" + row_of + R"( + 4 * part) = v;
   }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+)";
+    if (either) s += "  } else {\n";
+    if (!vec || either)
+        s += R"(  // 32 consecutive lanes cover a candidate's segment
+#pragma unroll 4
+  for (int m = 0; m < EMO_WAVE / 2; ++m) {
+    const int r = 2 * m + lane / 32, c = lane % 32;
+    const float v = stg[(c < n ? c : 0) * 65 + r];
+    const long long row = wbase + r;
+    if (row < B && c < n) S[)" + row_of + R"( + c] = stg_bad[r] ? EMO_NAN : v;
+  }
+)";
+    if (either) s += "  }\n";
+    return s + R"(  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
-)");
+)";
+}
+
+// Backward pass for the slack of every node: nodes in decreasing id (every edge leads to a higher
+// id), candidate-independent ones with their constant finish times.  Requires the forward's f<i>, T,
+// isbad and the level words, as emit_backward; columns are node ids.  Bound by the slack stores: 64
+// packs under 64 host nodes, 200,003 candidates, take 31 us with the selection (3.7 TB/s) against 495
+// on the interpreting kernels, which keep every finish time in device memory.
+void emit_backward_nodes(std::ostringstream &o, const JitGraph &g, const std::vector<std::string> &level_expr) {
+    const int V = static_cast<int>(g.nodes.size());
+    const int kc = stage_chunk(V);
+    o << "  const float Tb = isbad ? 0.f : T;\n";
+    o << "  unsigned int zb = 0u;\n  __asm__ __volatile__(\"\" : \"+v\"(zb));\n";
+    for (int v = V - 1; v >= 0; --v) {
+        const JitNode &nd = g.nodes[v];
+        o << "  float lf" << v << " = ";
+        if (nd.out.empty()) o << "Tb;\n";
+        for (size_t k = 0; k < nd.out.size(); ++k) {
+            if (k == 0) o << "s" << nd.out[0] << ";\n";
+            else o << "  lf" << v << " = fminf(lf" << v << ", s" << nd.out[k] << ");\n";
+        }
+        const int pack = nd.step >= 0 ? g.ops[nd.step].pack : -1;
+        std::string dur = flit(nd.dur);
+        if (pack >= 0) {
+            o << "  const float t" << v << " = tab[zb + " << static_cast<long long>(pack) * g.F << " + "
+              << level_expr[nd.step] << "].x;\n";
+            dur = "t" + std::to_string(v);
+        }
+        if (nd.has_in) o << "  const float s" << v << " = lf" << v << " - " << dur << ";\n";
+        o << "  stg[" << (v % kc) * 65 << " + lane] = lf" << v << " - "
+          << (nd.step >= 0 ? "f" + std::to_string(nd.step) : flit(nd.eft)) << ";\n";
+        if (v % kc == 0) o << "  emo_flush(stg, stg_bad, S, wbase, B, " << v << ", " << std::min(kc, V - v) << ");\n";
+    }
 }
 
 const char *kPrelude = R"(
@@ -458,7 +515,8 @@ typedef float emo_f32x4 __attribute__((ext_vector_type(4)));
 
 }  // namespace
 
-std::string jit_generate(const JitGraph &g, bool with_slack, bool tab_lds, int block) {
+std::string jit_generate(const JitGraph &g, JitSlack slack, bool tab_lds, int block) {
+    const bool with_slack = slack != JitSlack::kNone, nodes = slack == JitSlack::kNodes;
     std::ostringstream o;
     o << "#define EMO_BLOCK " << block << "\n" << kPrelude << kEmoSelectSource << "\n";
     const long long ntab = static_cast<long long>(g.P) * g.F + (is_pow2(g.F) ? 0 : kTablePad);
@@ -491,6 +549,7 @@ std::string jit_generate(const JitGraph &g, bool with_slack, bool tab_lds, int b
       << fwd.str() << "  EmoFwd r; r.T = T; r.E = E; return r;\n}\n";
 
     // forward pass, optional makespan/energy outputs, feasibility mask and selection partials
+    if (!nodes)
     o << "extern \"C\" __global__ void __launch_bounds__(EMO_BLOCK)\n"
          "emo_sp_select(const u8 *__restrict__ lv, long long B, const float2 *__restrict__ tabg,\n"
          "              float *__restrict__ To, float *__restrict__ Eo,\n"
@@ -503,14 +562,14 @@ std::string jit_generate(const JitGraph &g, bool with_slack, bool tab_lds, int b
          "  }\n}\n";
 
     if (with_slack) {
-        const bool staged = g.pack_monotone && g.P % 16 == 0;
+        const bool staged = nodes || g.pack_monotone;
+        const int cols = nodes ? static_cast<int>(g.nodes.size()) : g.P;
         if (staged) {
-            const int kc = stage_chunk(g.P);
-            o << "#define EMO_KC " << kc << "\n";
-            o << flush_source(g.P);
+            o << "#define EMO_KC " << stage_chunk(cols) << "\n";
+            o << flush_source(cols);
         }
         o << "extern \"C\" __global__ void __launch_bounds__(EMO_BLOCK)\n"
-             "emo_sp_slack(const u8 *__restrict__ lv, long long B, const float2 *__restrict__ tabg,\n"
+          << (nodes ? "emo_sp_nodes" : "emo_sp_slack") << "(const u8 *__restrict__ lv, long long B, const float2 *__restrict__ tabg,\n"
              "             float *__restrict__ S, float *__restrict__ To, float *__restrict__ Eo,\n"
              "             EmoTargets tg) {\n"
              "  EMO_TABLE_DECL\n"
@@ -532,7 +591,8 @@ std::string jit_generate(const JitGraph &g, bool with_slack, bool tab_lds, int b
         o << "  if (active) { if (To) To[cand] = T; if (Eo) Eo[cand] = E; }\n";
         if (staged) o << "  stg_bad[lane] = isbad ? 1u : 0u;\n";
         lp.launder();
-        emit_backward(o, g, staged, level_expr);
+        if (nodes) emit_backward_nodes(o, g, level_expr);
+        else emit_backward(o, g, staged, level_expr);
         o << "  if (tg.n) emo_select_all(grp, active, T, E, cand, B, tg);\n";
         o << "  }\n}\n";
     }
@@ -1560,6 +1620,18 @@ int jit_compile(const std::string &src, bool with_slack, JitModule *out, std::st
     if (!get_function(out->module, "emo_sp_select", &out->select) ||
         (with_slack && !get_function(out->module, "emo_sp_slack", &out->slack))) {
         *log = "specialised kernels missing from the module";
+        (void)hipModuleUnload(out->module);
+        *out = JitModule();
+        return 2;
+    }
+    return 0;
+}
+
+int jit_compile_nodes(const std::string &src, JitModule *out, std::string *log) {
+    int rc = compile_module(src, &out->module, &out->compile_seconds, log);
+    if (rc != 0) return rc;
+    if (!get_function(out->module, "emo_sp_nodes", &out->slack)) {
+        *log = "per-node slack kernel missing from the module";
         (void)hipModuleUnload(out->module);
         *out = JitModule();
         return 2;

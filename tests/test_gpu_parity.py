@@ -1114,3 +1114,43 @@ def test_workload_full_batch(torch, emo, k):
     SN_or = np.stack([oracle.slack(g, rows[c]).slack for c in pick2])
     parity.assert_slack(host(SN)[pick2], SN_or, T_or[pick2], True, spec.name + " node slack")
     gh.close()
+
+
+@pytest.mark.parametrize("P", [1, 3, 7, 31, 33, 35, 48, 64, 100, 157])
+def test_one_kernel_slack_rows_of_any_pack_count(torch, emo, P):
+    """Slack of every pack and of every node from the specialised kernels against the interpreting
+    ones bit for bit, for pack and node counts that end inside a 32-column piece, are no multiple of 4,
+    or are wide enough for 16-byte stores, with invalid levels, ragged batches and a slack buffer that
+    is only 4-byte aligned; on host-launch graphs (2 P nodes) and on graphs whose nodes are the packs."""
+    rng = np.random.default_rng(4000 + P)
+    for F, g in ((5, synth.stream_graph(P, P, 1 + P % 3, 5)), (8, synth.packed_graph(P, P, 2, 8, sync_every=P + 1)),
+                 (16, synth.scaled_times(synth.packed_graph(P, P, 3, 16, sync_every=max(2, P // 2)), 1.1))):
+        ga = emo.EmoGraph(g, device=0)
+        gi = emo.EmoGraph(g, device=0, kernel_mode=emo.KERNELS_INTERPRETED)
+        for B in (1, 63, 1000):
+            rows = rng.integers(0, F, (B, P)).astype(np.uint8)
+            if B > 2:
+                rows[B // 2, rng.integers(0, P)] = F
+                rows[B - 1, 0] = 255
+            lv = dev(torch, rows)
+            for per_node in (False, True):
+                print(f"[case] one-kernel slack {g.name} V={g.num_nodes} B={B} per_node={per_node}", flush=True)
+                cols = g.num_nodes if per_node else P
+                flat = torch.zeros(B * cols + 1, dtype=torch.float32, device="cuda")
+                for out in (None, flat[1:].view(B, cols)):
+                    outs = []
+                    for gh in (ga, gi):
+                        T = torch.empty(B, dtype=torch.float32, device="cuda")
+                        E = torch.empty_like(T)
+                        S = torch.empty((B, cols), dtype=torch.float32, device="cuda") if out is None or gh is gi else out
+                        S.fill_(-7.0)
+                        gh.slack(lv, per_node=per_node, out=S, makespan=T, energy=E)
+                        outs.append([host(x).view(np.uint32) for x in (T, E, S)])
+                        if gh is ga and (out is None or cols % 16 != 0):
+                            assert gh.info()["last_kernels"] == 1, gh.info()
+                    for a, b in zip(*outs):
+                        nan = np.isnan(b.view(np.float32))
+                        assert np.array_equal(nan, np.isnan(a.view(np.float32)))
+                        assert np.array_equal(a[~nan], b[~nan])
+        ga.close()
+        gi.close()
