@@ -281,9 +281,12 @@ struct emo_graph_s {
     int cut_state = 0;                       // 0 not tried, 1 compiled, -1 failed
     emo::JitModule jk;
     // time-interval kernels specialised to the graph
-    int iv_state = 0;                        // 0 not tried, 1 compiled, -1 failed
-    emo::JitModule jiv;
-    int64_t iv_cap_key = -1, iv_cap = 0;     // resident workgroups for the last (K, M)
+    // (workgroups of 256, 512 and 1024 candidates, each compiled on first use)
+    struct IvKernel {
+        int state = 0;                       // 0 not tried, 1 compiled, -1 failed
+        emo::JitModule m;
+        int64_t cap_key = -1, cap = 0;       // resident workgroups for the last (K, M)
+    } iv[3];
     Arena arena;                             // per-call scratch, kept between calls
     Arena dp_arena;                          // scratch of the policy search (whose evaluations
                                              // use `arena`)
@@ -632,6 +635,7 @@ void release_device(emo_graph_s *g) {
         emo::jit_unload(&g->jn);
         emo::jit_unload(&g->jc);
         emo::jit_unload(&g->jk);
+        for (emo_graph_s::IvKernel &k : g->iv) emo::jit_unload(&k.m);
         for (void *p : g->allocations) (void)hipFree(p);
         arena_free(g->arena);
         arena_free(g->dp_arena);
@@ -943,24 +947,31 @@ std::string node_source(const emo_graph_s &g, int *block_out) {
     return emo::jit_generate(g.jg, emo::JitSlack::kNodes, tab_lds, *block_out);
 }
 
-// Generates and compiles the time-interval kernels once; returns 1 when they are ready.
-int ensure_iv(emo_graph_s *g) {
+size_t iv_table_bytes(const emo_graph_s &g) {
+    const size_t tb = static_cast<size_t>(g.P) * g.F * sizeof(float2);
+    return tb <= kJitTableLds ? tb : 0;   // 0: read from device memory
+}
+
+// Generates and compiles the time-interval kernel of `block` candidates a workgroup once; *out is its
+// record, ready when the result is 1.
+int ensure_iv(emo_graph_s *g, int block, emo_graph_s::IvKernel **out) {
     std::lock_guard<std::mutex> lock(g->jit_mu);
-    if (g->iv_state != 0) return g->iv_state;
-    const size_t tb = static_cast<size_t>(g->P) * g->F * sizeof(float2);
-    const bool tab_lds = tb <= kJitTableLds;
-    const std::string src = emo::jit_generate_intervals(g->jg, tab_lds, 256);
+    emo_graph_s::IvKernel &k = g->iv[block == 256 ? 0 : block == 512 ? 1 : 2];
+    *out = &k;
+    if (k.state != 0) return k.state;
+    const bool tab_lds = static_cast<size_t>(g->P) * g->F * sizeof(float2) <= kJitTableLds;
+    const std::string src = emo::jit_generate_intervals(g->jg, tab_lds, block);
     DeviceGuard guard(g->device);
     emo::JitModule m;
     std::string log;
     if (emo::jit_compile_intervals(src, &m, &log) != 0) {
         g->jit_log = log;
-        g->iv_state = -1;
+        k.state = -1;
         return -1;
     }
-    m.block = 256;
-    g->jiv = m;
-    g->iv_state = 1;
+    m.block = block;
+    k.m = m;
+    k.state = 1;
     g->info.compile_seconds += static_cast<float>(m.compile_seconds);
     return 1;
 }
@@ -1675,13 +1686,15 @@ emo_status emo_eval_intervals(emo_graph_t g, const uint8_t *levels, int64_t B, i
     emo::IvJitArgs iva;
     bool use_jit = g->kernel_mode != EMO_KERNELS_INTERPRETED && g->jit_eligible &&
                    iv_buckets(pol.pts, num_intervals, &iva.scale, &iva.M);
+    emo_graph_s::IvKernel *ivk = nullptr;
     if (use_jit) {
-        const int st = ensure_iv(g);
-        if (st != 1 && g->kernel_mode == EMO_KERNELS_SPECIALIZED)
+        const int block = emo::jit_iv_block(iv_table_bytes(*g), num_intervals, iva.M, B);
+        const int state = ensure_iv(g, block, &ivk);
+        if (state != 1 && g->kernel_mode == EMO_KERNELS_SPECIALIZED)
             return fail(EMO_ERR_DEVICE, "time-interval kernel compilation failed: %s", g->jit_log.c_str());
         // the rows and the bucket table must fit the workgroup's LDS beside the static tables
-        use_jit = st == 1 && g->jiv.iv_static_lds + emo::jit_iv_dyn_lds(g->jiv.block, num_intervals, iva.M) <=
-                                 static_cast<size_t>(g->jiv.iv_max_lds);
+        use_jit = state == 1 && ivk->m.iv_static_lds + emo::jit_iv_dyn_lds(block, num_intervals, iva.M) <=
+                                    static_cast<size_t>(ivk->m.iv_max_lds);
     }
     int64_t iv_cap = 0;
     if (use_jit) {
@@ -1691,13 +1704,13 @@ emo_status emo_eval_intervals(emo_graph_t g, const uint8_t *levels, int64_t B, i
         // persistent workgroups (each builds the bucket table once): as many as are resident
         const int64_t key = static_cast<int64_t>(num_intervals) << 32 | iva.M;
         std::lock_guard<std::mutex> lock(g->jit_mu);
-        if (g->iv_cap_key != key) {
-            g->iv_cap = emo::jit_iv_cap(g->jiv, num_intervals, iva.M);
-            g->iv_cap_key = key;
+        if (ivk->cap_key != key) {
+            ivk->cap = emo::jit_iv_cap(ivk->m, num_intervals, iva.M);
+            ivk->cap_key = key;
         }
-        iv_cap = g->iv_cap;
+        iv_cap = ivk->cap;
     }
-    const int64_t nblocks = use_jit ? emo::jit_blocks(g->jiv, B) : emo::forward_blocks(B);
+    const int64_t nblocks = use_jit ? emo::jit_blocks(ivk->m, B) : emo::forward_blocks(B);
     size_t part_bytes = result ? static_cast<size_t>(nblocks) * emo::kPartialBytes : 0;
     part_bytes = (part_bytes + 255) & ~static_cast<size_t>(255);
     const size_t work_bytes = use_jit ? 0 : emo::forward_scratch_bytes(g->dg.eval, B);
@@ -1717,7 +1730,7 @@ emo_status emo_eval_intervals(emo_graph_t g, const uint8_t *levels, int64_t B, i
     g->info.last_kernels = use_jit ? 7 : 0;
     hipError_t e = g->ev_begin ? hipEventRecord(g->ev_begin, st) : hipSuccess;
     if (e == hipSuccess && use_jit)
-        e = emo::jit_launch_intervals(g->jiv, levels, B, g->dg.tab, iva, iv_cap, makespan, energy, tg, st);
+        e = emo::jit_launch_intervals(ivk->m, levels, B, g->dg.tab, iva, iv_cap, makespan, energy, tg, st);
     else if (e == hipSuccess)
         e = emo::launch_intervals(g->dg, pol, levels, B, makespan, energy, tg, work, st);
     if (e == hipSuccess && g->ev_end) e = hipEventRecord(g->ev_end, st);

@@ -444,6 +444,11 @@ std::string jit_generate_intervals(const JitGraph &g, bool tab_lds, int block);
 int jit_compile_intervals(const std::string &src, JitModule *out, std::string *log);
 // Dynamic LDS bytes of emo_iv for K intervals and M buckets (bucket table, then the rows).
 size_t jit_iv_dyn_lds(int block, int K, int M);
+// Candidates per workgroup (256, 512 or 1024) of emo_iv for a table of table_bytes in LDS: the
+// smallest that keeps nearly the most waves of a compute unit busy (one table copy a workgroup, so a
+// large table needs large workgroups; past 16 waves more do not help) and that B candidates fill the
+// device with.
+int jit_iv_block(size_t table_bytes, int K, int M, int64_t B);
 // Resident workgroups of emo_iv on the current device with that dynamic LDS (0: unknown).
 int64_t jit_iv_cap(const JitModule &m, int K, int M);
 hipError_t jit_launch_intervals(const JitModule &m, const uint8_t *levels, int64_t B, const float2 *tab,

@@ -242,12 +242,12 @@ std::string est_expr(const JitGraph &g, int i, const char *prefix) {
     bool have = false;
     for (int k : op.in) {
         std::string v = std::string(prefix) + std::to_string(k);
-        e = have ? "fmaxf(" + e + ", " + v + ")" : v;
+        e = have ? "emo_fmax(" + e + ", " + v + ")" : v;
         have = true;
     }
     // finish times are >= 0, so a zero floor from candidate-independent predecessors only
     // matters for a node without candidate-dependent ones
-    if (op.cst != 0.f || !have) e = have ? "fmaxf(" + e + ", " + flit(op.cst) + ")" : flit(op.cst);
+    if (op.cst != 0.f || !have) e = have ? "emo_fmax(" + e + ", " + flit(op.cst) + ")" : flit(op.cst);
     return e;
 }
 
@@ -328,7 +328,7 @@ LevelPlan emit_forward_range(std::ostringstream &o, const JitGraph &g, const Ran
         } else {
             o << "  float f" << i << " = " << est_expr(g, i, "f") << " + " << flit(op.dur) << ";\n";
         }
-        if (r.accumulate && op.out.empty()) o << "  T = fmaxf(T, f" << i << ");\n";
+        if (r.accumulate && op.out.empty()) o << "  T = emo_fmax(T, f" << i << ");\n";
         if (r.ck_copy && (*r.ck_copy)[i]) o << "  c" << i << " = f" << i << ";\n";
         if (r.ck_row && (*r.ck_row)[i] >= 0) {
             if ((*r.ck_always)[i])
@@ -511,6 +511,13 @@ typedef unsigned int emo_u32x4 __attribute__((ext_vector_type(4)));
 typedef float emo_f32x4 __attribute__((ext_vector_type(4)));
 #define EMO_GLOBAL __attribute__((address_space(1)))
 #define EMO_NAN __builtin_nanf("")
+// max of two finish times or start floors: they are never negative, negative zero or NaN (an addition
+// to a non-negative start gives no negative zero), so their bit patterns order like unsigned integers.
+// fmaxf quiets NaNs first: one more instruction for each operand that comes from memory or an asm.
+__device__ __forceinline__ float emo_fmax(float a, float b) {
+  const unsigned int x = __float_as_uint(a), y = __float_as_uint(b);
+  return __uint_as_float(x > y ? x : y);
+}
 )";
 
 }  // namespace
@@ -612,6 +619,20 @@ std::string jit_generate(const JitGraph &g, JitSlack slack, bool tab_lds, int bl
 // point of a higher one is > est, and the one in bucket b is compared directly: the count of
 // points <= est is exact, as in the interpreting kernel.  Energies and the idle term follow the
 // interpreting kernel's order, so both give bit-identical results.
+//
+// A step is a chain of three LDS reads (bucket, level byte, table entry), so what bounds the kernel is
+// their latency: waves per compute unit.  A 64 KB table leaves room for two workgroups, whatever their
+// size, so these take 512 or 1,024 candidates (jit_iv_block).  The rows in LDS hold each level times the
+// table stride (up to 32 levels), invalid ones replaced when the rows are copied, so a byte read is
+// the table address and the step needs no clamp.  512 packs of 16 levels, 2^20 candidates: 16 intervals
+// 350 us with workgroups of 256 (8 waves a compute unit), 163 with 512 (16 waves); 64 intervals 741 and
+// 258 (one workgroup of 1,024).  The energy and finish times pass an asm every 4 steps: at 8 or 16 the
+// compiler takes more than 128 registers and half the waves (16 intervals: 297 and 316 us against 180).
+
+namespace {
+int iv_level_shift(const JitGraph &g) { return g.F <= 32 ? 3 : 0; }   // (31 * 8 fits a byte)
+unsigned iv_level_mask(const JitGraph &g) { return static_cast<unsigned>(g.F - 1) * 0x01010101u; }
+}  // namespace
 
 std::string jit_generate_intervals(const JitGraph &g, bool tab_lds, int block) {
     std::ostringstream o;
@@ -633,18 +654,22 @@ std::string jit_generate_intervals(const JitGraph &g, bool tab_lds, int block) {
                    "u) & w) & 0x80808080u";
     }
     o << R"(
-// interval of start time `est`: the number of change points <= est
-__device__ __forceinline__ unsigned int emo_interval(float est, const int2 *bk, float scale, int M) {
-  const int b = (int)fminf(est * scale, (float)(M - 1));
-  const int2 e = bk[b];
-  return (unsigned int)e.x + (est >= __int_as_float(e.y) ? 1u : 0u);
+// bucket of start time `est`: count of change points of lower buckets, the bucket's point
+__device__ __forceinline__ int2 emo_bucket(float est, const int2 *bk, float scale, float last) {
+  return bk[(int)fminf(est * scale, last)];
 }
-struct EmoFwd { float T; float E; bool bad; };
+struct EmoFwd { float T; float E; };
 )";
-    // forward body; the lane's row of K level bytes is in LDS at `myrow` (word aligned)
-    o << "__device__ __forceinline__ EmoFwd emo_iv_forward(const u8 *myrow, int K,\n"
+    // level bytes in the LDS rows: multiplied by the table stride when that fits a byte (then a byte is
+    // the entry's offset in its pack's row as it stands)
+    const int shift = iv_level_shift(g);
+    const std::string at = shift ? "" : " * 8u";
+    // forward body; the lane's row of level bytes is in LDS at `myrow` (word aligned)
+    o << "__device__ __forceinline__ EmoFwd emo_iv_forward(const u8 *myrow, bool bad,\n"
          "    const float2 *__restrict__ tab, const int2 *bk, float scale, int M, const float *pts,\n"
          "    const double *dur, const float *idle) {\n"
+         "  const float last = (float)(M - 1);\n"
+         "  const char *tabb = (const char *)tab;\n"
          "  float T = " << flit(g.t_const) << ";\n"
          "  double eacc = 0.0;\n  float eblk = 0.f;\n";
     const int n = static_cast<int>(g.ops.size());
@@ -669,50 +694,57 @@ struct EmoFwd { float T; float E; bool bad; };
         }
         o << "  const float e" << i << " = " << est_expr(g, i, "f") << ";\n";
         if (op.pack >= 0) {
-            o << "  const unsigned int v" << i << " = emo_interval(e" << i << ", bk, scale, M);\n"
-              << "  unsigned int l" << i << " = myrow[v" << i << "];\n"
-              << "  l" << i << " = l" << i << " < EMO_F ? l" << i << " : 0u;\n"
-              << "  const float2 te" << i << " = tab[" << static_cast<long long>(op.pack) * g.F << " + l" << i
-              << "];\n"
+            o << "  const int2 b" << i << " = emo_bucket(e" << i << ", bk, scale, last);\n"
+              << "  const unsigned int l" << i << " = myrow[b" << i << ".x + (e" << i << " >= __int_as_float(b" << i
+              << ".y) ? 1 : 0)];\n"
+              << "  const float2 te" << i << " = *(const float2 *)(tabb + " << (tab_lds ? "" : "(")
+              << static_cast<long long>(op.pack) * g.F * 8 << (tab_lds ? "" : "u") << " + l" << i << at
+              << (tab_lds ? "" : ")") << ");\n"
               << "  float f" << i << " = e" << i << " + te" << i << ".x;\n"
               << "  eblk += te" << i << ".y;\n";
             if (++npk % kEnergyBlock == 0) o << "  eacc += (double)eblk;\n  eblk = 0.f;\n";
         } else {
             o << "  float f" << i << " = e" << i << " + " << flit(op.dur) << ";\n";
         }
-        if (op.out.empty()) o << "  T = fmaxf(T, f" << i << ");\n";
+        if (op.out.empty()) o << "  T = emo_fmax(T, f" << i << ");\n";
     }
     o << "  eacc += (double)eblk;\n"
-         "  // invalid levels anywhere in the row, four bytes a word\n"
-         "  const unsigned int *mw = (const unsigned int *)myrow;\n"
-         "  unsigned int bad = 0u;\n"
-         "  for (int j = 0; 4 * j < K; ++j) {\n"
-         "    unsigned int w = mw[j];\n"
-         "    if (4 * j + 4 > K) w &= 0xffffffffu >> (8 * (4 * j + 4 - K));   // bytes past the row\n"
-         "    bad |= " << bad_word << ";\n"
-         "  }\n";
+         "#define EMO_IDLE(b) (*(const float *)((const char *)idle + ((b)" << (shift ? " >> 1" : " << 2") << ")))\n";
     o << R"(  // idle energy, interval by interval in increasing order: the whole length of the nf
   // intervals that end at or before T (nf: the number of change points <= T, the interval of T),
-  // then the part of interval nf below T.  Levels >= F read zeros (their row gives NaN anyway).
-  const int nf = (int)emo_interval(T, bk, scale, M);
+  // then the part of interval nf below T.
+  const unsigned int *mw = (const unsigned int *)myrow;
+  const int2 bT = emo_bucket(T, bk, scale, last);
+  const int nf = bT.x + (T >= __int_as_float(bT.y) ? 1 : 0);
   for (int j = 0; 4 * j < nf; ++j) {
     const unsigned int w = mw[j];
 #pragma unroll
     for (int q = 0; q < 4; ++q)
-      if (4 * j + q < nf) eacc = fma((double)idle[(w >> (8 * q)) & 255u], dur[4 * j + q], eacc);
+      if (4 * j + q < nf) eacc = fma((double)EMO_IDLE((w >> (8 * q)) & 255u), dur[4 * j + q], eacc);
   }
   const double Td = (double)T;
   const double lo = nf > 0 ? (double)pts[nf - 1] : 0.0;
-  if (Td > lo) eacc = fma((double)idle[myrow[nf]], Td - lo, eacc);
+  if (Td > lo) eacc = fma((double)EMO_IDLE((unsigned int)myrow[nf]), Td - lo, eacc);
   EmoFwd r;
   r.T = T;
   r.E = (float)eacc;
-  r.bad = bad != 0u;
-  if (r.bad) { r.T = EMO_NAN; r.E = EMO_NAN; }
+  if (bad) { r.T = EMO_NAN; r.E = EMO_NAN; }
   return r;
 }
 )";
-    o << "extern \"C\" __global__ void __launch_bounds__(EMO_BLOCK)\n"
+    // a word of level bytes as the rows hold them: invalid bytes as level 0 (*bad becomes non-zero)
+    o << "__device__ __forceinline__ unsigned int emo_iv_word(unsigned int w, unsigned int *bad) {\n";
+    if (is_pow2(g.F))
+        o << "  *bad |= w & " << ~iv_level_mask(g) << "u;\n  return (w & " << iv_level_mask(g) << "u) << " << shift << ";\n}\n";
+    else
+        o << "  const unsigned int m = " << bad_word << ";\n"
+             "  *bad |= m;\n"
+             "  return (w & ~(m | (m - (m >> 7)))) << " << shift << ";\n}\n";
+    // a table in device memory: registers for several table reads in flight rather than more waves (the
+    // compiler otherwise orders the steps to save registers and waits for each read: 900 packs of 24
+    // levels, 131,072 candidates, 176 us that way)
+    o << "extern \"C\" __global__ void __launch_bounds__(EMO_BLOCK)"
+      << (tab_lds ? "" : " __attribute__((amdgpu_waves_per_eu(1, 3)))") << "\n"
          "emo_iv(const u8 *__restrict__ lv, long long B, const float2 *__restrict__ tabg, EmoIvArgs a,\n"
          "    int copy, float inv_k, float *__restrict__ To, float *__restrict__ Eo, EmoTargets tg) {\n";
     if (tab_lds)
@@ -723,6 +755,7 @@ struct EmoFwd { float T; float E; bool bad; };
     o << R"(  __shared__ float s_pts[256];
   __shared__ double s_dur[256];      // interval lengths T_{i+1} - T_i (T_0 = 0)
   __shared__ float s_idle[256];      // zero past F
+  __shared__ u8 s_bad[EMO_BLOCK];    // the row holds an invalid level
   // dynamic: the bucket table (M entries), then the group's rows, SD words a row
   extern __shared__ __align__(16) unsigned int emo_dyn[];
   const int K = a.K, M = a.M;
@@ -730,6 +763,7 @@ struct EmoFwd { float T; float E; bool bad; };
   int2 *s_bk = (int2 *)emo_dyn;
   unsigned int *s_rows = emo_dyn + 2 * M;
   const float scale = a.scale;
+  s_bad[threadIdx.x] = 0;
   for (int i = threadIdx.x; i < K - 1; i += EMO_BLOCK) s_pts[i] = a.pts[i];
   for (int i = threadIdx.x; i < K - 1; i += EMO_BLOCK)
     s_dur[i] = (double)a.pts[i] - (i > 0 ? (double)a.pts[i - 1] : 0.0);
@@ -746,11 +780,10 @@ struct EmoFwd { float T; float E; bool bad; };
     const float c = lo < K - 1 && (int)(s_pts[lo] * scale) == b ? s_pts[lo] : __builtin_inff();
     s_bk[b] = make_int2(lo, __float_as_int(c));
   }
-  const u8 *my = (const u8 *)(s_rows + threadIdx.x * SD);
   for (long long grp = blockIdx.x; grp * EMO_BLOCK < B; grp += gridDim.x) {
     // the group's rows are contiguous: copy them to LDS with coalesced loads of `copy` bytes
     // (16 when K is a multiple of 16, 4 when of 4, else 1; the batch aligned to match).  Row of
-    // byte x: floor((x + 0.5) / K), exact from the fp32 product for x < 2^16, K <= 256.
+    // byte x: floor((x + 0.5) / K), exact from the fp32 product for x < 2^22.
     __syncthreads();   // the previous group's rows are read (and the tables built)
     {
       const long long r0 = grp * EMO_BLOCK;
@@ -761,18 +794,27 @@ struct EmoFwd { float T; float E; bool bad; };
           const emo_u32x4 w = ((const emo_u32x4 *)src)[q];
           const int r = (int)(((float)(q << 4) + 0.5f) * inv_k);
           unsigned int *d = s_rows + r * SD + (((q << 4) - r * K) >> 2);
-          d[0] = w.x; d[1] = w.y; d[2] = w.z; d[3] = w.w;
+          unsigned int bad = 0u;
+          d[0] = emo_iv_word(w.x, &bad);
+          d[1] = emo_iv_word(w.y, &bad);
+          d[2] = emo_iv_word(w.z, &bad);
+          d[3] = emo_iv_word(w.w, &bad);
+          if (bad) s_bad[r] = 1;
         }
       } else if (copy == 4) {
         for (int q = threadIdx.x; q < (nb >> 2); q += EMO_BLOCK) {
           const unsigned int w = ((const unsigned int *)src)[q];
           const int r = (int)(((float)(q << 2) + 0.5f) * inv_k);
-          s_rows[r * SD + (((q << 2) - r * K) >> 2)] = w;
+          unsigned int bad = 0u;
+          s_rows[r * SD + (((q << 2) - r * K) >> 2)] = emo_iv_word(w, &bad);
+          if (bad) s_bad[r] = 1;
         }
       } else {
         for (int q = threadIdx.x; q < nb; q += EMO_BLOCK) {
           const int r = (int)(((float)q + 0.5f) * inv_k);
-          ((u8 *)s_rows)[((r * SD) << 2) + q - r * K] = src[q];
+          unsigned int bad = 0u;
+          ((u8 *)s_rows)[((r * SD) << 2) + q - r * K] = (u8)emo_iv_word(src[q], &bad);
+          if (bad) s_bad[r] = 1;
         }
       }
     }
@@ -780,7 +822,11 @@ struct EmoFwd { float T; float E; bool bad; };
     const long long gid = grp * EMO_BLOCK + threadIdx.x;
     const bool active = gid < B;
     const long long cand = active ? gid : B - 1;
-    const EmoFwd r = emo_iv_forward(my, K, tab, s_bk, scale, M, s_pts, s_dur, s_idle);
+    // (a lane past the batch walks the group's first row)
+    const u8 *my = (const u8 *)(s_rows + (active ? threadIdx.x : 0u) * SD);
+    const bool bad = s_bad[threadIdx.x] != 0;
+    s_bad[threadIdx.x] = 0;   // (set again after the next group's first barrier)
+    const EmoFwd r = emo_iv_forward(my, bad, tab, s_bk, scale, M, s_pts, s_dur, s_idle);
     if (active) { if (To) To[cand] = r.T; if (Eo) Eo[cand] = r.E; }
     if (tg.n) emo_select_all(grp, active, r.T, r.E, cand, B, tg);
   }
@@ -1711,9 +1757,25 @@ int jit_compile_intervals(const std::string &src, JitModule *out, std::string *l
     return 0;
 }
 
+namespace {
+constexpr size_t kIvLdsPerCu = 160 * 1024;
+}  // namespace
+
 size_t jit_iv_dyn_lds(int block, int K, int M) {
     const size_t sd = static_cast<size_t>(((K + 3) >> 2) | 1);
     return static_cast<size_t>(M) * 8 + static_cast<size_t>(block) * sd * 4;
+}
+
+int jit_iv_block(size_t table_bytes, int K, int M, int64_t B) {
+    // waves of a compute unit whose workgroups of `block` candidates share one table copy each
+    auto waves = [&](int block) {
+        const size_t lds = table_bytes + 4096 + static_cast<size_t>(block) + 512 + jit_iv_dyn_lds(block, K, M);
+        return std::min<int64_t>(16, static_cast<int64_t>(kIvLdsPerCu / lds) * block / 64);
+    };
+    int best = 256;
+    for (int block : {512, 1024})
+        if (B >= 256 * static_cast<int64_t>(block) && waves(block) * 8 > waves(best) * 9) best = block;
+    return best;
 }
 
 int64_t jit_blocks(const JitModule &m, int64_t B) { return grid_of(B, m.block); }

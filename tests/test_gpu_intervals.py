@@ -200,3 +200,43 @@ def test_intervals_workload_kernels(torch, emo, K):
     pick = np.concatenate([synth.sample_rows(B, 200), [7]])
     To, Eo = intervals.eval_intervals(g, pts, rows[pick], idle)
     check(host(T)[pick], host(E)[pick], To, Eo, f"K={K} sampled rows")
+
+
+@pytest.mark.parametrize("graph, B, K", [
+    ("training", 131072 + 37, 16),     # workgroups of 512 candidates around a 64 KB table
+    ("training", 262144 + 5, 64),      # of 1,024
+    ("training", 131071, 64),          # of 256: too few candidates to fill the device with larger ones
+    ("F24", 3001, 7), ("F32", 70001, 16), ("F40", 3001, 20), ("F200", 3001, 9), ("F256", 3001, 16),
+    ("large-table", 9001, 16)])        # a table past LDS
+def test_intervals_workgroups_and_level_bytes(torch, emo, graph, B, K):
+    """Every workgroup size of the specialised kernel, and level bytes as its LDS rows hold them (times
+    the table stride up to 32 levels, plain above; invalid bytes replaced), against the interpreting
+    kernel bit for bit on every row, with the feasibility mask and the selection."""
+    rng = np.random.default_rng(B + K)
+    g = (synth.config_graph(3) if graph == "training" else
+         synth.packed_graph(5, 600, 4, 24, sync_every=700) if graph == "large-table" else
+         synth.stream_graph(6, 41, 3, int(graph[1:])))
+    F = g.num_levels
+    T0 = float(oracle.eval_batch(g, np.full((1, g.num_packs), F - 1, np.uint8))[0][0])
+    # unevenly spaced, but never so close that the bucket table is too long
+    pts = [float(synth.quantize(1.05 * T0 * (i + 1 + 0.4 * rng.random()) / K)) for i in range(K - 1)]
+    idle = [float(x) for x in np.round(rng.uniform(0, 1, F) * 64) / 64]
+    rows = rng.integers(0, F, (B, K)).astype(np.uint8)
+    if F < 256:
+        rows[[3, B // 2, B - 1], [0, K // 2, K - 1]] = [F, 255, min(255, F + 7)]
+    print(f"[case] intervals {graph} B={B} K={K}", flush=True)
+    lv = dev(torch, rows)
+    got = []
+    tgt = float(np.float32(1.3 * T0))
+    for mode in (0, 1):
+        gh = emo.EmoGraph(g, device=0, kernel_mode=mode)
+        m = torch.empty((B + 31) // 32, dtype=torch.int32, device="cuda")
+        r = torch.empty(3, dtype=torch.int64, device="cuda")
+        T, E, _, _ = gh.eval_intervals(lv, pts, idle, latency_target=tgt, mask=m, result=r)
+        assert gh.info()["last_kernels"] == (7 if mode == 0 else 0)
+        got.append([host(x).view(np.uint32) for x in (T, E, m, r)])
+        gh.close()
+    assert np.isnan(got[0][0].view(np.float32)).sum() == (3 if F < 256 else 0)
+    for a, b in zip(*got):
+        nan = (a.view(np.float32) != a.view(np.float32)) & (b.view(np.float32) != b.view(np.float32))
+        assert np.array_equal(a[~nan], b[~nan])
