@@ -119,8 +119,7 @@ typedef struct {
                                      time-interval kernel
                                      specialised to the graph (emo_eval_intervals; 0 there
                                      means the interpreting kernel), 8 two-pass chain scan
-                                     whose window copies and slack stores follow per-thread
-                                     plans fixed for the call (chain_scan_full), 9 one-kernel
+                                     with every window full (chain_scan_full), 9 one-kernel
                                      policy search (emo_dp_search; another kind there is the
                                      evaluator of a search by stages) */
     int32_t chain_lanes;          /* lanes per candidate of the chain-lane kernels, 0 when the
@@ -134,9 +133,7 @@ typedef struct {
                                      back to an earlier window, fewer than 16 packs); calls
                                      without slack use it on graphs that neither one kernel nor
                                      the segmented kernels take, when levels and slack are
-                                     16-byte aligned (rows of a
-                                     pack count that is not a multiple of 16 are copied from
-                                     the dwords around each 16-byte piece) */
+                                     16-byte aligned */
     int32_t cut_segments;         /* segments of the cut-segment kernels, 0 when they do not
                                      apply.  A cut node is one that every other node precedes
                                      or follows (an all-stream synchronisation): no path
@@ -161,13 +158,10 @@ typedef struct {
                                      windowed layout); calls with slack use it on graphs of at
                                      least 768 steps (the segmented kernels, slower there, take
                                      161-767) when levels and slack are 16-byte aligned */
-    int32_t chain_scan_full;      /* 1 when slack calls of the two-pass chain scan run the
-                                     kernel with per-thread copy plans (last_kernels 8): every
-                                     window lies wholly inside the graph (P a multiple of
-                                     chain_scan_window), a thread holds at most four 16-byte
-                                     pieces of a window's slack tile (at least
-                                     chain_scan_window / 16 chains) and a workgroup's slack
-                                     rows span less than 4 GiB; 0 otherwise */
+    int32_t chain_scan_full;      /* 1 when slack calls of the two-pass chain scan are reported
+                                     as last_kernels 8: every window lies wholly inside the
+                                     graph (P a multiple of chain_scan_window) and there are
+                                     at least chain_scan_window / 16 chains; 0 otherwise */
     int32_t hip_runtime_version;  /* hipRuntimeGetVersion of the HIP runtime the library runs
                                      on (e.g. 70051831 for 7.0.51831).  The run-time compiler
                                      of the specialised kernels is the hiprtc of that same

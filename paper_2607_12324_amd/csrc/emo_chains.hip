@@ -24,6 +24,7 @@
 #include <stdint.h>
 
 #include <atomic>
+#include <type_traits>
 
 #include "emo_internal.h"
 
@@ -359,7 +360,7 @@ gather_slack(const float *__restrict__ tmp, const int32_t *__restrict__ pos, int
 // written in chain order and gathered.  The windowed kernel cuts the pack ids into windows of
 // W packs instead and turns the layout around: a wave is 64 candidates on ONE chain, and a
 // workgroup is G groups of 64 candidates x nc chains.  Per window the workgroup copies into
-// LDS, with 16-byte loads issued two windows ahead into registers:
+// LDS, with 16-byte loads issued one or two windows ahead into registers:
 //   - the G*64 candidates' level bytes of the window (checked against F on the way),
 //   - the window's table rows (time and energy; times only in the second pass),
 //   - the window's step block: where each chain's steps start, and the step records.
@@ -368,13 +369,13 @@ gather_slack(const float *__restrict__ tmp, const int32_t *__restrict__ pos, int
 // writes each step's slack into an LDS tile [candidate][column] that the workgroup writes out in
 // pack order with 16-byte stores.
 //
-// Column W of every level row is 0 and row W of the table is zero, so a fixed node (column W)
+// A wave's steps are read 16 at a time, one per lane of every row of 16 lanes, and handed on by
+// broadcast operands.  Column W of every level row is 0 and row W of the table is zero, so a fixed node (column W)
 // reads a zero time and energy and adds its own duration; its tile entry is column W's pad.
 // Energies are summed per chain in fp32 over each window, added into fp64, and the chains'
 // sums are added in chain order.
-constexpr int kWinPre = 4;                         // 16-byte prefetch pieces per thread and window
 constexpr size_t kWinLds = 150 * 1024;
-constexpr size_t kWinSpare = 1024;                   // chains_scan_full: 16 spare bytes per lane
+constexpr size_t kWinSpare = 1024;                   // 16 spare bytes per lane
 constexpr int kWinMaxWaves = 16;
 
 __host__ __device__ inline uint32_t round16u(uint32_t x) { return (x + 15u) & ~15u; }
@@ -438,168 +439,22 @@ __device__ __forceinline__ float fmax_nonneg(float a, float b) {
 struct WinArgs {
     int W, wlog, nc, NC, F;
     int blk_bytes, hdr_words;
-    int slots_lvl, slots_tab8, slots_tab4, slots_blk;   // prefetch slots per category
     WinLayout L;
 };
 
-// Prefetch slots of each category for nt threads; false when they exceed kWinPre.
-__host__ __device__ inline bool win_slots(int W, int NC, int F, int blk_bytes, int nt, int *sl, int *st8,
-                                          int *st4, int *sb) {
-    *sl = (NC * (W / 16) + nt - 1) / nt;
-    *st8 = (W * F / 2 + nt - 1) / nt;
-    *st4 = (W * F / 4 + nt - 1) / nt;
-    *sb = (blk_bytes / 16 + nt - 1) / nt;
-    return *sl + *st8 + *sb <= kWinPre;
-}
-
-// One window's copy in flight: the thread's pieces (16 bytes each), slot by slot: the first
-// slots hold level rows, the next table rows, the next the step block (how many of each is the
-// same for every thread, so the category of a slot is uniform); which of them read as zero
-// (level columns past P, table rows past the last pack, pieces past the end).  Rows of a pack
-// count that is not a multiple of 16 are not 16-byte aligned (the layout then gives every
-// thread one level piece, in slot 0): the piece is the five dwords around it (v[0] and x, from
-// its address rounded down to 4 bytes), and meta holds its byte shift (2 bits) and its number
-// of bytes before the row's end (5 bits).
-struct WinSet {
-    uint4 v[kWinPre];
-    uint32_t x;
-    uint32_t zero;
-    uint32_t meta;
+// 16-byte pieces a thread of nt copies per window: level rows, the table (forward), the table
+// (second pass), the step block.
+struct WinSlots {
+    int lvl, tab8, tab4, blk;
+    __host__ __device__ int total() const { return lvl + tab8 + blk; }
 };
-
-// Issues exactly kWinPre loads for window w (a piece past the end reads a valid address and is
-// zeroed when stored; unused slots read the first block piece), with the addresses as scalar
-// bases plus 32-bit lane offsets, so that the compiler counts them and waits at a commit for
-// the older window's loads only.  esize: bytes per table entry (8 forward, 4 backward).
-template <bool ROWS16>
-__device__ __forceinline__ void win_load(const WinArgs &a, const uint8_t *__restrict__ levels,
-                                         const void *__restrict__ tab, int esize,
-                                         const uint4 *__restrict__ blocks, int64_t base, int64_t B,
-                                         int32_t P, int w, WinSet &s) {
-    const int t = threadIdx.x, nt = blockDim.x;
-    const int rlog = a.wlog - 4;                                   // pieces per level row: W / 16
-    const int n_lvl = a.NC << rlog;
-    const int n_tab = (a.W * a.F * esize) >> 4;
-    const int n_blk = a.blk_bytes >> 4;
-    const int s_lvl = a.slots_lvl, s_tab = esize == 8 ? a.slots_tab8 : a.slots_tab4;
-    const int64_t wcol = static_cast<int64_t>(w) << a.wlog;
-    const uint8_t *lbase = levels + base * P + wcol;               // window's first column, row base
-    const int64_t tab_off = wcol * a.F * esize;                    // bytes
-    const uint32_t tab_left = static_cast<uint32_t>(static_cast<int64_t>(P) * a.F * esize - tab_off);
-    const char *tbase = static_cast<const char *>(tab) + tab_off;
-    const char *bbase = reinterpret_cast<const char *>(blocks + static_cast<int64_t>(w) * n_blk);
-    const int64_t rows_left = B - base;                             // rows of this workgroup in range
-    const int64_t cols_left = P - wcol;
-    uint32_t zero = 0u, meta = 0u;
-#pragma unroll
-    for (int i = 0; i < kWinPre; ++i) {
-        const char *src;
-        uint32_t off;
-        bool z;
-        if (i < s_lvl) {
-            const int q = t + i * nt;
-            const int r = q >> rlog, k = q - (r << rlog);
-            const int rr = r < rows_left ? r : static_cast<int>(rows_left - 1);
-            z = q >= n_lvl || 16 * k >= cols_left;
-            off = z ? 0u : static_cast<uint32_t>(rr) * static_cast<uint32_t>(P) + 16u * static_cast<uint32_t>(k);
-            src = reinterpret_cast<const char *>(lbase);
-            if (!ROWS16 && i == 0) {
-                // the five dwords from the piece's address rounded down to 4 bytes; a dword at or
-                // past the last one of the batch's rows reads that last dword instead (its bytes
-                // are all past the row's end, and masked when stored)
-                const uint64_t at = reinterpret_cast<uint64_t>(src + off);
-                const uint64_t lo = reinterpret_cast<uint64_t>(levels);
-                const uint64_t last = (lo + static_cast<uint64_t>(B * P) + 3u) / 4u * 4u - 4u;
-                const uint64_t al = at & ~static_cast<uint64_t>(3);
-                uint32_t d[5];
-#pragma unroll
-                for (int j = 0; j < 5; ++j) {
-                    const uint64_t aj = al + 4u * j;
-                    d[j] = *reinterpret_cast<const uint32_t *>(aj <= last ? aj : last);
-                }
-                s.v[0] = make_uint4(d[0], d[1], d[2], d[3]);
-                s.x = d[4];
-                const int64_t nb = cols_left - 16 * k;
-                meta = static_cast<uint32_t>(at & 3u) | (static_cast<uint32_t>(nb < 16 ? (nb > 0 ? nb : 0) : 16) << 2);
-                zero |= z ? 1u << i : 0u;
-                continue;
-            }
-        } else if (i < s_lvl + s_tab) {
-            const int q = t + (i - s_lvl) * nt;
-            z = q >= n_tab || 16u * static_cast<uint32_t>(q) >= tab_left;
-            off = z ? 0u : 16u * static_cast<uint32_t>(q);
-            src = tbase;
-        } else {
-            const int q = t + (i - s_lvl - s_tab) * nt;
-            z = q >= n_blk || i >= s_lvl + s_tab + a.slots_blk;
-            off = z ? 0u : 16u * static_cast<uint32_t>(q);
-            src = bbase;
-        }
-        zero |= z ? 1u << i : 0u;
-        s.v[i] = *reinterpret_cast<const uint4 *>(src + off);
-    }
-    s.zero = zero;
-    s.meta = meta;
-}
-
-// A level piece of an unaligned row from its five dwords: the 16 bytes at the piece's shift,
-// with the bytes past the row's end cleared.
-__device__ __forceinline__ uint4 win_piece(const WinSet &s) {
-    const uint32_t sh = s.meta & 3u, nb = (s.meta >> 2) & 31u;
-    uint32_t o[4];
-    o[0] = __builtin_amdgcn_alignbyte(s.v[0].y, s.v[0].x, sh);
-    o[1] = __builtin_amdgcn_alignbyte(s.v[0].z, s.v[0].y, sh);
-    o[2] = __builtin_amdgcn_alignbyte(s.v[0].w, s.v[0].z, sh);
-    o[3] = __builtin_amdgcn_alignbyte(s.x, s.v[0].w, sh);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const uint32_t keep = nb >= 4u * j + 4u ? 4u : (nb > 4u * j ? nb - 4u * j : 0u);   // bytes kept
-        o[j] &= keep == 4u ? 0xffffffffu : (1u << (8u * keep)) - 1u;
-    }
-    return make_uint4(o[0], o[1], o[2], o[3]);
-}
-
-// Copies window w's pieces into LDS buffer `buf`; a level byte >= F marks its candidate in `bad`
-// when it is given (the forward pass).  Such a byte is not cleared: the candidate's makespan,
-// energy and slack become NaN whatever its lookups read, and a lookup at column c <= W with
-// level l <= 255 stays inside the workgroup's LDS (at most 255 entries past the window's table,
-// which the layout leaves room for).
-template <bool ROWS16>
-__device__ __forceinline__ void win_store(const WinArgs &a, char *lds, int buf, void *tabbuf, int esize,
-                                          uint32_t *bad, uint32_t addf, const WinSet &s) {
-    const int t = threadIdx.x, nt = blockDim.x;
-    const int rlog = a.wlog - 4;
-    const int n_lvl = a.NC << rlog;
-    const int n_tab = (a.W * a.F * esize) >> 4;
-    const int n_blk = a.blk_bytes >> 4;
-    const int s_lvl = a.slots_lvl, s_tab = esize == 8 ? a.slots_tab8 : a.slots_tab4;
-    uint8_t *lvl = reinterpret_cast<uint8_t *>(lds) + buf * a.L.lvl_buf;
-    uint4 *blk = reinterpret_cast<uint4 *>(lds + a.L.off_blk + buf * a.blk_bytes);
-#pragma unroll
-    for (int i = 0; i < kWinPre; ++i) {
-        uint4 v = !ROWS16 && i == 0 ? win_piece(s) : s.v[i];
-        if ((s.zero >> i) & 1u) v = make_uint4(0u, 0u, 0u, 0u);
-        if (i < s_lvl) {
-            const int q = t + i * nt;
-            if (q < n_lvl) {
-                const int r = q >> rlog, k = q - (r << rlog);
-                uint32_t *d = reinterpret_cast<uint32_t *>(lvl + r * a.L.lvl_pitch + 16 * k);
-                d[0] = v.x;
-                d[1] = v.y;
-                d[2] = v.z;
-                d[3] = v.w;
-                if (bad && (bad_levels(v.x, addf) | bad_levels(v.y, addf) | bad_levels(v.z, addf) |
-                            bad_levels(v.w, addf)))
-                    bad[r] = 1u;
-            }
-        } else if (i < s_lvl + s_tab) {
-            const int q = t + (i - s_lvl) * nt;
-            if (q < n_tab) reinterpret_cast<uint4 *>(tabbuf)[q] = v;
-        } else if (i < s_lvl + s_tab + a.slots_blk) {
-            const int q = t + (i - s_lvl - s_tab) * nt;
-            if (q < n_blk) blk[q] = v;
-        }
-    }
+__host__ __device__ inline WinSlots win_slots(int W, int NC, int F, int blk_bytes, int nt) {
+    WinSlots s;
+    s.lvl = (NC * (W / 16) + nt - 1) / nt;
+    s.tab8 = (W * F / 2 + nt - 1) / nt;
+    s.tab4 = (W * F / 4 + nt - 1) / nt;
+    s.blk = (blk_bytes / 16 + nt - 1) / nt;
+    return s;
 }
 
 // Buffer resources of the planned copies: raw buffer accesses with a 32-bit per-lane offset and a
@@ -614,37 +469,38 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t win_rsrc(const void *base, uin
 // stays below 2^31 too): loads there read zeros and stores are dropped.
 constexpr uint32_t kWinNoStore = 0x80000000u;
 
-// The copy of a window wholly inside the graph (its W columns and table rows all exist), with
-// each thread's pieces at offsets fixed for the whole kernel: win_plan computes them once, and a
-// window then costs its loads, its stores and a few scalar operations.  A thread with no piece
-// in a slot loads past the slot's buffer (the range check returns zeros without touching memory)
-// and stores them to its lane's spare 16 bytes at LDS offset `spare` (so every load is waited
-// for and every store made on every path, which keeps the compiler's count of loads in flight
-// exact).
+// The copy of a window, with each thread's pieces at offsets fixed for the whole kernel: win_plan
+// computes them once, and a window then costs its loads, its stores and a few scalar operations.
+// A thread with no piece in a table or block slot loads past the slot's buffer (the range check
+// returns zeros without touching memory) and stores them to its lane's spare 16 bytes at LDS
+// offset `spare` (so every load is waited for and every store made on every path, which keeps the
+// compiler's count of loads in flight exact).  Level pieces are plain loads (of any alignment: a row
+// of P bytes may start anywhere); a thread without one loads row 0's first piece.
+template <int NL, int NT, int NB>
 struct WinPlan {
-    uint32_t src[kWinPre];    // byte offset of the piece in its slot's per-window source
-    uint32_t dst0[kWinPre];   // LDS byte offset of the piece in buffer 0 (or the spare)
-    uint32_t dst1[kWinPre];   // in buffer 1
+    static constexpr int kSlots = NL + NT + NB;
+    uint32_t src[kSlots];     // byte offset of the piece in its slot's per-window source
+    uint32_t dst0[kSlots];    // LDS byte offset of the piece in buffer 0 (or the spare)
+    uint32_t dst1[kSlots];    // in buffer 1
     uint32_t has;             // bit i: the thread has a piece in slot i
 };
 
-template <int NT>
-__device__ __forceinline__ WinPlan win_plan(const WinArgs &a, int esize, int64_t rows_left, int32_t P,
-                                            uint32_t spare) {
+template <int NL, int NT, int NB>
+__device__ __forceinline__ WinPlan<NL, NT, NB> win_plan(const WinArgs &a, int esize, int64_t rows_left, int32_t P,
+                                                        uint32_t spare) {
     const int t = threadIdx.x, nt = blockDim.x;
     const int rlog = a.wlog - 4;
     const int n_lvl = a.NC << rlog;
     const int n_tab = (a.W * a.F * esize) >> 4;
     const int n_blk = a.blk_bytes >> 4;
-    const int s_lvl = 1, s_tab = NT;
     const uint32_t own = spare + 16u * static_cast<uint32_t>(t & 63);
-    WinPlan p;
+    WinPlan<NL, NT, NB> p;
     p.has = 0u;
 #pragma unroll
-    for (int i = 0; i < kWinPre; ++i) {
+    for (int i = 0; i < NL + NT + NB; ++i) {
         bool ok = false;
         uint32_t src = 0u, d0 = 0u, stride = 0u;
-        if (i < s_lvl) {
+        if (i < NL) {
             const int q = t + i * nt;
             const int r = q >> rlog, k = q - (r << rlog);
             const int rr = r < rows_left ? r : static_cast<int>(rows_left - 1);
@@ -652,22 +508,22 @@ __device__ __forceinline__ WinPlan win_plan(const WinArgs &a, int esize, int64_t
             src = static_cast<uint32_t>(rr) * static_cast<uint32_t>(P) + 16u * static_cast<uint32_t>(k);
             d0 = static_cast<uint32_t>(r) * a.L.lvl_pitch + 16u * static_cast<uint32_t>(k);
             stride = a.L.lvl_buf;
-        } else if (i < s_lvl + s_tab) {
-            const int q = t + (i - s_lvl) * nt;
+        } else if (i < NL + NT) {
+            const int q = t + (i - NL) * nt;
             ok = q < n_tab;
             src = 16u * static_cast<uint32_t>(q);
             d0 = a.L.off_x + 16u * static_cast<uint32_t>(q);
             stride = a.L.tab_elems * static_cast<uint32_t>(esize);
-        } else if (i == s_lvl + s_tab) {
-            const int q = t + (i - s_lvl - s_tab) * nt;
+        } else {
+            const int q = t + (i - NL - NT) * nt;
             ok = q < n_blk;
             src = 16u * static_cast<uint32_t>(q);
             d0 = a.L.off_blk + 16u * static_cast<uint32_t>(q);
             stride = static_cast<uint32_t>(a.blk_bytes);
         }
         // an absent piece reads past its buffer's end (zeros, with no memory traffic)
-        p.src[i] = ok ? src : kWinNoStore;
-        p.dst0[i] = ok ? d0 : own;   // (slots past those in use: ok is false, the spare slot)
+        p.src[i] = ok ? src : (i < NL ? 0u : kWinNoStore);
+        p.dst0[i] = ok ? d0 : own;
         p.dst1[i] = ok ? d0 + stride : own;
         p.has |= ok ? 1u << i : 0u;
     }
@@ -677,54 +533,106 @@ __device__ __forceinline__ WinPlan win_plan(const WinArgs &a, int esize, int64_t
 // The per-workgroup buffers of a pass's planned copies: the workgroup's level rows, the pass's
 // table (8-byte entries forward, 4-byte in the second pass) and the step blocks.
 struct WinBufs {
-    __amdgpu_buffer_rsrc_t lvl, tab, blk;
+    const uint8_t *lvl;
+    __amdgpu_buffer_rsrc_t tab, blk;
     int32_t tab_win;   // table bytes per window: W * F * esize
 };
 
-// Issues the loads of window w (wholly inside the graph) from the plan.  The slots are fixed at
-// compile time: slot 0 levels, slots 1 .. NT the table, slot NT + 1 the step block.
-template <int NT>
-__device__ __forceinline__ void win_load_full(const WinArgs &a, const WinPlan &p, const WinBufs &b, int w,
-                                              WinSet &s) {
+// One window's copy in flight.
+template <int N>
+struct WinSet {
+    uint4 v[N];
+};
+
+// The bytes by which the thread's level piece in slot i reaches past its row's end in the last
+// window: the load is moved back by as many, so that it ends with the row (P >= 16), and the store
+// drops its first bytes.
+__device__ __forceinline__ int win_over(const WinArgs &a, uint32_t has, int i, int w, int32_t P) {
+    const int q = (has >> i) & 1u ? static_cast<int>(threadIdx.x) + i * static_cast<int>(blockDim.x) : 0;
+    const int end = (w << a.wlog) + 16 * (q & ((1 << (a.wlog - 4)) - 1)) + 16;
+    return end > P ? end - P : 0;
+}
+
+typedef unsigned int emo_u4a1 __attribute__((ext_vector_type(4), aligned(1)));
+
+// Issues the loads of window w from the plan.  RAG: the last window may reach past the rows.
+template <bool RAG, int NL, int NT, int NB>
+__device__ __forceinline__ void win_load(const WinArgs &a, const WinPlan<NL, NT, NB> &p, const WinBufs &b, int w,
+                                         int nwin, int32_t P, WinSet<NL + NT + NB> &s) {
     // the window offsets are uniform; readfirstlane says so to the compiler (an offset it takes
     // for divergent becomes a loop over the distinct values around each load)
     const int so_lvl = __builtin_amdgcn_readfirstlane(w << a.wlog);
     const int so_tab = __builtin_amdgcn_readfirstlane(w * b.tab_win);
     const int so_blk = __builtin_amdgcn_readfirstlane(w * a.blk_bytes);
+    const uint8_t *lbase = b.lvl + so_lvl;
+    uint32_t back[NL];
 #pragma unroll
-    for (int i = 0; i < NT + 2; ++i) {
+    for (int i = 0; i < NL; ++i) back[i] = 0u;
+    if (RAG && w == nwin - 1) {
+#pragma unroll
+        for (int i = 0; i < NL; ++i) back[i] = static_cast<uint32_t>(win_over(a, p.has, i, w, P));
+    }
+#pragma unroll
+    for (int i = 0; i < NL + NT + NB; ++i) {
         emo_u4 v;
-        if (i == 0) v = __builtin_amdgcn_raw_buffer_load_b128(b.lvl, p.src[i], so_lvl, 0);
-        else if (i <= NT) v = __builtin_amdgcn_raw_buffer_load_b128(b.tab, p.src[i], so_tab, 0);
-        else v = __builtin_amdgcn_raw_buffer_load_b128(b.blk, p.src[i], so_blk, 0);
+        if (i < NL) {
+            // (RAG: the base is 256 bytes lower, so that the offset stays non-negative)
+            const uint8_t *src = RAG ? lbase - 256 + (p.src[i] + 256u - back[i]) : lbase + p.src[i];
+            if (RAG) v = *reinterpret_cast<const emo_u4a1 *>(src);
+            else v = *reinterpret_cast<const emo_u4 *>(src);
+        } else if (i < NL + NT) {
+            v = __builtin_amdgcn_raw_buffer_load_b128(b.tab, p.src[i], so_tab, 0);
+        } else {
+            v = __builtin_amdgcn_raw_buffer_load_b128(b.blk, p.src[i], so_blk, 0);
+        }
         s.v[i] = make_uint4(v.x, v.y, v.z, v.w);
     }
-    s.zero = 0u;
 }
 
-// Stores a window loaded by win_load_full<NT> at the plan's destinations `dst` (its dst0 or
-// dst1), with no branches.  In the forward pass (`badbits` given) the thread's level piece with
-// a byte >= F sets bit 0 of *badbits; the caller marks the rows at the end of the pass.  hib: the
-// bits of a byte at or above F when F is a power of two (then one mask test), else 0.
-template <int NT>
-__device__ __forceinline__ void win_store_full(const WinPlan &p, const uint32_t *dst, char *lds,
-                                               uint32_t *badbits, uint32_t addf, uint32_t hib, const WinSet &s) {
+// v without its first n bytes, zeros behind (all zeros for n >= 16)
+__device__ __forceinline__ uint4 drop_bytes(uint4 v, int n) {
+    unsigned long long lo = static_cast<unsigned long long>(v.y) << 32 | v.x;
+    unsigned long long hi = static_cast<unsigned long long>(v.w) << 32 | v.z;
+    if (n >= 8) {
+        lo = n >= 16 ? 0ull : hi;
+        hi = 0ull;
+        n = n >= 16 ? 0 : n - 8;
+    }
+    if (n > 0) {
+        lo = lo >> (8 * n) | hi << (64 - 8 * n);
+        hi >>= 8 * n;
+    }
+    return make_uint4(static_cast<uint32_t>(lo), static_cast<uint32_t>(lo >> 32), static_cast<uint32_t>(hi),
+                      static_cast<uint32_t>(hi >> 32));
+}
+
+// Stores window w, loaded by win_load, at the plan's destinations `dst` (its dst0 or dst1), level
+// bytes shifted left by SH (the scale of a table entry; 0: as they are).  In the forward pass
+// (`badbits` given) a level piece with a byte >= F sets its slot's bit; the caller marks the rows at
+// the end of the pass.  hib: the bits of a byte at or above F when F is a power of two (then one
+// mask test), else 0.
+template <bool RAG, int SH, int NL, int NT, int NB>
+__device__ __forceinline__ void win_store(const WinArgs &a, const WinPlan<NL, NT, NB> &p, const uint32_t *dst,
+                                          char *lds, int w, int nwin, int32_t P, uint32_t *badbits, uint32_t addf,
+                                          uint32_t hib, const WinSet<NL + NT + NB> &s) {
+    constexpr uint32_t keep = ((0xffu << SH) & 0xffu) * 0x01010101u;
 #pragma unroll
-    for (int i = 0; i < NT + 2; ++i) {
-        const uint4 v = s.v[i];
-        if (i == 0) {
+    for (int i = 0; i < NL + NT + NB; ++i) {
+        uint4 v = s.v[i];
+        if (i < NL) {
+            if (RAG && w == nwin - 1) v = drop_bytes(v, win_over(a, p.has, i, w, P));
             if (badbits) {
                 const uint32_t b = hib ? (v.x | v.y | v.z | v.w) & hib
                                        : bad_levels(v.x, addf) | bad_levels(v.y, addf) | bad_levels(v.z, addf) |
                                              bad_levels(v.w, addf);
-                *badbits |= b && (p.has & 1u) ? 1u : 0u;
+                *badbits |= b && (p.has >> i & 1u) ? 1u << i : 0u;
             }
             // level rows are 4-byte aligned (odd pitch in words)
-            uint32_t *d = reinterpret_cast<uint32_t *>(lds + dst[0]);
-            d[0] = v.x;
-            d[1] = v.y;
-            d[2] = v.z;
-            d[3] = v.w;
+            uint32_t *d = reinterpret_cast<uint32_t *>(lds + dst[i]);
+            d[0] = (v.x << SH) & keep;
+            d[1] = (v.y << SH) & keep;
+            d[2] = (v.z << SH) & keep;
+            d[3] = (v.w << SH) & keep;
         } else {
             *reinterpret_cast<uint4 *>(lds + dst[i]) = v;
         }
@@ -733,35 +641,36 @@ __device__ __forceinline__ void win_store_full(const WinPlan &p, const uint32_t 
 
 // Marks the rows of the forward pass's level pieces that held a byte >= F (after the pass; the
 // caller's barrier then makes bad[] complete).
+template <int NL>
 __device__ __forceinline__ void win_mark_bad(const WinArgs &a, uint32_t badbits, uint32_t *bad) {
-    const int t = threadIdx.x, nt = blockDim.x;
-    const int rlog = a.wlog - 4;
-    (void)nt;
-    if (badbits & 1u) bad[t >> rlog] = 1u;
+#pragma unroll
+    for (int i = 0; i < NL; ++i)
+        if (badbits >> i & 1u)
+            bad[(static_cast<int>(threadIdx.x) + i * static_cast<int>(blockDim.x)) >> (a.wlog - 4)] = 1u;
 }
 
-// The slack tile's flush when every window lies wholly inside the graph, with each thread's (at
-// most four) pieces at LDS and global offsets fixed for the whole kernel: piece j of the thread
-// is float4 piece q = t + j * nt of the tile in the order of the general flush.  Global offsets
-// are bytes from the workgroup's first row at the window's first column (32-bit: NC * P * 4 <
-// 2^32).
+// The slack tile's flush, with each thread's (at most NF) 16-byte pieces at LDS and global offsets
+// fixed for the whole kernel: a wave covers 4 candidates x 16 pieces when rows are long enough
+// (conflict-free LDS reads with the odd row pitch), else whole rows.  Global offsets are bytes from
+// the workgroup's first row at the window's first column (32-bit); slack rows are 4-byte aligned.
+template <int NF>
 struct FlushPlan {
-    uint32_t src[4];   // LDS byte offset of the piece's first float
-    uint32_t dst[4];   // byte offset in the slack rows
-    uint32_t has;      // bit j: the piece exists and its row is in the batch
-    uint32_t nan;      // bit j: the piece's candidate has an invalid level (its slack row is NaN)
+    uint32_t src[NF];   // LDS byte offset of the piece's first float
+    uint32_t dst[NF];   // byte offset in the slack rows
+    uint32_t nan;       // bit j: the piece's candidate has an invalid level (its slack row is NaN)
 };
 
 // (after the forward pass: tfin holds the makespans, NaN for a candidate with an invalid level)
-__device__ __forceinline__ FlushPlan flush_plan(const WinArgs &a, int64_t rows_left, int32_t P, const float *tfin) {
+template <int NF>
+__device__ __forceinline__ FlushPlan<NF> flush_plan(const WinArgs &a, int64_t rows_left, int32_t P,
+                                                    const float *tfin) {
     const int t = threadIdx.x, nt = blockDim.x;
     const int W = a.W, prlog = a.wlog - 2;
     const int n = a.NC << prlog;
-    FlushPlan f;
-    f.has = 0u;
+    FlushPlan<NF> f;
     f.nan = 0u;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < NF; ++j) {
         const int q = t + j * nt;
         int r, kk;
         if (prlog >= 4) {
@@ -777,7 +686,6 @@ __device__ __forceinline__ FlushPlan flush_plan(const WinArgs &a, int64_t rows_l
         f.src[j] = ok ? a.L.off_tile + 4u * static_cast<uint32_t>(r * (W + 1) + 4 * kk) : a.L.off_tile;
         f.dst[j] = ok ? 4u * (static_cast<uint32_t>(r) * static_cast<uint32_t>(P) + 4u * static_cast<uint32_t>(kk))
                       : kWinNoStore;
-        f.has |= ok ? 1u << j : 0u;
         const float tr = tfin[ok ? r : 0];
         f.nan |= ok && tr != tr ? 1u << j : 0u;
     }
@@ -787,17 +695,38 @@ __device__ __forceinline__ FlushPlan flush_plan(const WinArgs &a, int64_t rows_l
 // `rows`: the workgroup's slack rows (S from its first row, a range check at the batch's end);
 // pieces a thread does not have and rows past the batch store at kWinNoStore, which the range
 // check drops, so no store needs a lane mask
-__device__ __forceinline__ void flush_full(const FlushPlan &f, __amdgpu_buffer_rsrc_t rows, const char *lds, int w,
-                                           int wlog) {
-    const int so = (w << wlog) * 4;
+template <int NF>
+__device__ __forceinline__ void flush_window(const FlushPlan<NF> &f, __amdgpu_buffer_rsrc_t rows, const char *lds,
+                                             int w, int wlog) {
+    // (the window's offset is added to the lanes' offsets: with a scalar offset the compiler lets the
+    // next instruction overwrite the third or fourth data register of a 16-byte store, and the store
+    // was seen to write the new value; with none it keeps the wait state that such a store needs)
+    const uint32_t so = static_cast<uint32_t>(w << wlog) * 4u;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < NF; ++j) {
         const float *src = reinterpret_cast<const float *>(lds + f.src[j]);
         float4 v = make_float4(src[0], src[1], src[2], src[3]);
         if ((f.nan >> j) & 1u) v = make_float4(__builtin_nanf(""), __builtin_nanf(""), __builtin_nanf(""),
                                                __builtin_nanf(""));
         const emo_u4 u = {__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z), __float_as_uint(v.w)};
-        __builtin_amdgcn_raw_buffer_store_b128(u, rows, f.dst[j], so, 0);
+        __builtin_amdgcn_raw_buffer_store_b128(u, rows, f.dst[j] + so, 0, 0);
+    }
+}
+
+// The last window's flush when it reaches past the rows: a float a lane, consecutive lanes on
+// consecutive columns.
+__device__ __forceinline__ void flush_last(const WinArgs &a, __amdgpu_buffer_rsrc_t rows, const char *lds,
+                                           const float *tfin, int w, int64_t rows_left, int32_t P) {
+    const int W = a.W, cols = P - (w << a.wlog);
+    const float *tile = reinterpret_cast<const float *>(lds + a.L.off_tile);
+    for (int q = threadIdx.x; q < a.NC << a.wlog; q += blockDim.x) {
+        const int r = q >> a.wlog, cc = q & (W - 1);
+        const float v = tfin[r] != tfin[r] ? __builtin_nanf("") : tile[r * (W + 1) + cc];
+        const uint32_t dst = r < rows_left && cc < cols
+                                 ? 4u * (static_cast<uint32_t>(r) * static_cast<uint32_t>(P) +
+                                         static_cast<uint32_t>((w << a.wlog) + cc))
+                                 : kWinNoStore;
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rows, dst, 0, 0);
     }
 }
 
@@ -812,33 +741,115 @@ __device__ __forceinline__ void win_range(const WinArgs &a, const char *lds, int
 // would otherwise sink the next groups' reads and serialise the round trips again).
 __device__ __forceinline__ void win_issue_point() { asm volatile("" ::: "memory"); }
 
-// Four consecutive steps of the wave's chain: their records (column and table offset, start
-// floor, fixed duration) and, once read, the candidate's level bytes at their columns.  A chain's
-// steps in a window come in whole groups (padded with no-op steps), and every block has 8 no-op
-// steps on both sides, so reading up to two groups beyond a chain's range stays in the block.
+// x of lane J of the lane's row of 16 lanes (every lane active)
+template <int J>
+__device__ __forceinline__ uint32_t row_bcast(uint32_t x) {
+    return static_cast<uint32_t>(
+        __builtin_amdgcn_update_dpp(0, static_cast<int>(x), 0x150 + J, 0xf, 0xf, true));
+}
+
+// Sixteen consecutive steps of the wave's chain, one per lane of every row of 16 lanes: the LDS
+// address of the step's column in the first level row and of its table row, its start floor and its
+// fixed duration.  A step's fields reach all lanes as the broadcast operand of the
+// instruction that uses them, so a step costs no read of its record.
 template <bool FIXED>
-struct WinGroup {
-    uint32_t ct[4];
-    float cst[4];
-    float dur[4];
-    unsigned lv[4];
-    __device__ __forceinline__ void read(const ChainWinStep *rs, int k) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const uint2 v = *reinterpret_cast<const uint2 *>(rs + k + i);
-            ct[i] = v.x;
-            cst[i] = __uint_as_float(v.y);
-            if (FIXED) dur[i] = rs[k + i].dur;
-        }
-    }
-    __device__ __forceinline__ void levels(const uint8_t *lrow) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) lv[i] = lrow[ct[i] & 0xffffu];
-    }
+struct WinChunk {
+    uint32_t col, tab, cst, dur;
 };
 
-// Slack (the two-pass scan) comes from a second forward pass instead of a backward one.  Along
-// a chain with durations
+// ESH: log2 of a table entry's bytes.
+template <bool FIXED, int ESH>
+__device__ __forceinline__ WinChunk<FIXED> win_chunk(const ChainWinStep *rs, int k, int kmax, uint32_t lvl_base,
+                                                     uint32_t tab_base) {
+    const int i = k + static_cast<int>(threadIdx.x & 15u);
+    const ChainWinStep *r = rs + (i < kmax ? i : kmax);   // (kmax: the block's last no-op step)
+    const uint2 v = *reinterpret_cast<const uint2 *>(r);
+    WinChunk<FIXED> c;
+    c.col = (v.x & 0xffffu) + lvl_base;
+    c.tab = ((v.x >> 16) << ESH) + tab_base;
+    c.cst = v.y;
+    c.dur = FIXED ? __float_as_uint(r->dur) : 0u;
+    return c;
+}
+
+// LDS by address: the sums above are whole addresses (with a pointer the compiler adds the base last,
+// and the broadcast becomes an instruction of its own).
+typedef float emo_f2 __attribute__((ext_vector_type(2)));
+template <typename T>
+__device__ __forceinline__ T lds_at(uint32_t at) {
+    return *(const __attribute__((address_space(3))) T *)static_cast<uintptr_t>(at);
+}
+
+__device__ __forceinline__ void lds_put(uint32_t at, float x) {
+    *(__attribute__((address_space(3))) float *)static_cast<uintptr_t>(at) = x;
+}
+
+// The level bytes of steps 4J .. 4J + 3 of a chunk (lrow: the lane's row offset) and their table
+// entries.
+template <int J, bool FIXED>
+__device__ __forceinline__ void chunk_levels(const WinChunk<FIXED> &c, uint32_t lrow, uint32_t *lv) {
+    lv[0] = lds_at<uint8_t>(row_bcast<4 * J>(c.col) + lrow);
+    lv[1] = lds_at<uint8_t>(row_bcast<4 * J + 1>(c.col) + lrow);
+    lv[2] = lds_at<uint8_t>(row_bcast<4 * J + 2>(c.col) + lrow);
+    lv[3] = lds_at<uint8_t>(row_bcast<4 * J + 3>(c.col) + lrow);
+}
+
+// SH: what is left to scale a level by (0 when the staged bytes are scaled).
+template <int J, int SH, typename E, bool FIXED>
+__device__ __forceinline__ void chunk_table(const WinChunk<FIXED> &c, const uint32_t *lv, E *te) {
+    te[0] = lds_at<E>(row_bcast<4 * J>(c.tab) + (lv[0] << SH));
+    te[1] = lds_at<E>(row_bcast<4 * J + 1>(c.tab) + (lv[1] << SH));
+    te[2] = lds_at<E>(row_bcast<4 * J + 2>(c.tab) + (lv[2] << SH));
+    te[3] = lds_at<E>(row_bcast<4 * J + 3>(c.tab) + (lv[3] << SH));
+}
+
+// Walks the chain's steps k0 .. k1 - 1 (whole groups of four, padded with no-op steps) of a window:
+// use(integral_constant<int, j>, chunk, entry) for step j of its chunk.  The next group's table
+// entries and the level bytes of the group after it are in flight while a group is used; the groups
+// past k1 that are read belong to other chains or are no-op steps, and are not used.
+// after_chunk(c0): after 16 steps.
+template <bool FIXED, int ESH, int SH, typename E, typename Use, typename After>
+__device__ __forceinline__ void win_walk(const ChainWinStep *rs, int k0, int k1, int kmax,
+                                         uint32_t lvl_base, uint32_t tab_base, uint32_t lrow, Use use, After after) {
+    if (k0 >= k1) return;
+    WinChunk<FIXED> c = win_chunk<FIXED, ESH>(rs, k0, kmax, lvl_base, tab_base);
+    uint32_t l0[4], l1[4];
+    E t0[4], t1[4];
+    chunk_levels<0>(c, lrow, l0);
+    chunk_levels<1>(c, lrow, l1);
+    chunk_table<0, SH>(c, l0, t0);
+    for (int k = k0;; k += 16) {
+        const WinChunk<FIXED> n = win_chunk<FIXED, ESH>(rs, k + 16, kmax, lvl_base, tab_base);
+#define EMO_USE4(J, T)                                     \
+    win_issue_point();                                     \
+    use(std::integral_constant<int, 4 * J>(), c, T[0]);     \
+    use(std::integral_constant<int, 4 * J + 1>(), c, T[1]); \
+    use(std::integral_constant<int, 4 * J + 2>(), c, T[2]); \
+    use(std::integral_constant<int, 4 * J + 3>(), c, T[3])
+        chunk_table<1, SH>(c, l1, t1);
+        chunk_levels<2>(c, lrow, l0);
+        EMO_USE4(0, t0);
+        if (k + 4 >= k1) return;
+        chunk_table<2, SH>(c, l0, t0);
+        chunk_levels<3>(c, lrow, l1);
+        EMO_USE4(1, t1);
+        if (k + 8 >= k1) return;
+        chunk_table<3, SH>(c, l1, t1);
+        chunk_levels<0>(n, lrow, l0);
+        EMO_USE4(2, t0);
+        if (k + 12 >= k1) return;
+        chunk_table<0, SH>(n, l0, t0);
+        chunk_levels<1>(n, lrow, l1);
+        EMO_USE4(3, t1);
+        if (k + 16 >= k1) return;
+        after(k - k0);
+        c = n;
+#undef EMO_USE4
+    }
+}
+
+// Makespan and energy of stream-chain graphs, and with SLACK the slack of every pack.  Slack comes
+// from a second forward pass instead of a backward one.  Along a chain with durations
 // d_j and start floors cst_j, a step's only successor is the next step, so its latest finish is
 // the makespan minus the durations after it; with Pre_i = d_1 + ... + d_i and Tot = Pre_n,
 //   slack_i = LFT_i - EFT_i = (T - Tot) - (EFT_i - Pre_i),
@@ -850,251 +861,25 @@ struct WinGroup {
 // size, and every other value takes one rounding: slack agrees with the backward recurrence to
 // rounding, and bit for bit when every time sum is exact (every time a multiple of one power of
 // two u and every path below 2^24 u, so every sum and difference is exact in fp32 in any order).
-template <bool SLACK, bool FIXED, bool ROWS16>
-__global__ void __launch_bounds__(kChainBlockThreads)
+//
+// RAG: P is not a multiple of W (the last window reaches past the rows, and rows may start at any
+// byte).  SCALED (F <= 32): level bytes are staged as byte offsets into a table row.  NL, NT, NB:
+// 16-byte pieces of levels, forward table and step block a thread copies per window, DEPTH windows
+// ahead.
+//
+// What bounds it: the second pass its memory pattern (16,384 candidates of 65,536 kernels: 1.07 ms for
+// 1.07 GB read and 4.3 GB written in 1 KB pieces of 64 rows), the first pass latency and LDS.  A step used
+// to read its 8-byte record from LDS in every lane (four of about ten LDS cycles a step) and to take
+// nine instructions; with the records in the lanes of each row of 16 it takes six and no record read:
+// first pass 680 -> 532 us (no slack), with slack 1,671 -> 1,600; and pack counts that are no multiple of
+// the window, which took dword-wise copies and stores of one float a lane, take the same planned
+// 16-byte accesses: 2,043 kernels on 6 streams, 100,003 candidates 979 -> 452 us, 4,097 on 9 streams
+// 1,490 -> 670.
+template <bool SLACK, bool FIXED, bool RAG, bool SCALED, int NL, int NT, int NB, int DEPTH>
+__global__ void __launch_bounds__(kChainBlockThreads, DEPTH == 1 ? 6 : 4)
 chains_windowed(DevGraph g, DevChains c, WinArgs a, const uint4 *__restrict__ blocks,
                 const uint8_t *__restrict__ levels, int64_t B, float *__restrict__ To,
                 float *__restrict__ Eo, float *__restrict__ S) {
-    extern __shared__ float4 smem[];
-    char *lds = reinterpret_cast<char *>(smem);
-    const int t = threadIdx.x, nt = blockDim.x;
-    const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int grp = wv / a.nc, ch = wv - grp * a.nc;
-    const int lane = t & 63;
-    const int cl = grp * 64 + lane;                               // candidate within the workgroup
-    const int64_t base = static_cast<int64_t>(blockIdx.x) * a.NC;
-    const int64_t gc = base + cl;                                 // the candidate
-    const int W = a.W, F = a.F, nc = a.nc, nwin = c.nwin;
-    const int32_t P = g.P;
-    const WinLayout &L = a.L;
-    uint8_t *lvl0 = reinterpret_cast<uint8_t *>(lds);             // [2][NC][W + 4] bytes
-    uint32_t *bad = reinterpret_cast<uint32_t *>(lds + L.off_bad);
-    float *tfin = reinterpret_cast<float *>(lds + L.off_tfin);
-    float2 *tab2 = reinterpret_cast<float2 *>(lds + L.off_x);     // forward: [2][W + 1][F]
-    float *tabt = reinterpret_cast<float *>(lds + L.off_x);       // backward: [2][W + 1][F]
-    float *tile = reinterpret_cast<float *>(lds + L.off_tile);    // backward: [NC][W + 1]
-    const uint32_t addf = (0x80u - static_cast<uint32_t>(F)) * 0x01010101u;
-    auto recs = [&](int buf) {
-        return reinterpret_cast<const ChainWinStep *>(lds + L.off_blk + buf * a.blk_bytes + 4 * a.hdr_words);
-    };
-
-    // ------------------------------------------------------------------ forward
-    for (int i = t; i < a.NC; i += nt) {
-        bad[i] = 0u;
-        *reinterpret_cast<uint32_t *>(lvl0 + i * L.lvl_pitch + W) = 0u;
-        *reinterpret_cast<uint32_t *>(lvl0 + L.lvl_buf + i * L.lvl_pitch + W) = 0u;
-    }
-    for (int i = t; i < F; i += nt) {
-        tab2[W * F + i] = make_float2(0.f, 0.f);
-        tab2[L.tab_elems + W * F + i] = make_float2(0.f, 0.f);
-    }
-    WinSet s0, s1;
-    win_load<ROWS16>(a, levels, g.tab, 8, blocks, base, B, P, 0, s0);
-    win_load<ROWS16>(a, levels, g.tab, 8, blocks, base, B, P, nwin > 1 ? 1 : 0, s1);
-    lds_barrier();
-    win_store<ROWS16>(a, lds, 0, tab2, 8, bad, addf, s0);
-    lds_barrier();
-    float f = 0.f, pre = 0.f;
-    double ed = 0.0;
-    // window w from buffer w & 1; `ld` takes window w + 2, `cm` holds window w + 1
-    auto forward_window = [&](int w, WinSet &ld, WinSet &cm) {
-        const int buf = w & 1;
-        win_load<ROWS16>(a, levels, g.tab, 8, blocks, base, B, P, w + 2 < nwin ? w + 2 : nwin - 1, ld);
-        const uint8_t *lrow = lvl0 + buf * L.lvl_buf + cl * L.lvl_pitch;
-        const char *tb = reinterpret_cast<const char *>(tab2 + buf * L.tab_elems);
-        const ChainWinStep *rs = recs(buf);
-        int k0, k1;
-        win_range(a, lds, buf, ch, k0, k1);
-        float eb = 0.f;
-        const int ng = (k1 - k0) >> 2;
-        // group g of 4 steps: its table entries are read while the next group's level bytes and
-        // the records of the group after it are in flight
-        auto stage = [&](WinGroup<FIXED> &A, WinGroup<FIXED> &Bn, WinGroup<FIXED> &C, int g) {
-            float2 te[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                te[i] = *reinterpret_cast<const float2 *>(tb + (((A.ct[i] >> 16) + A.lv[i]) << 3));
-            Bn.levels(lrow);
-            C.read(rs, k0 + 4 * (g + 2));
-            win_issue_point();
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                f = fmax_nonneg(f, A.cst[i]) + te[i].x;
-                if (FIXED) f += A.dur[i];
-                eb += te[i].y;
-                if (SLACK) {
-                    pre += te[i].x;
-                    if (FIXED) pre += A.dur[i];
-                }
-            }
-        };
-        WinGroup<FIXED> G0, G1, G2;
-        G0.read(rs, k0);
-        G1.read(rs, k0 + 4);
-        G0.levels(lrow);
-        // fp32 energy blocks of at most 60 steps (15 groups, a whole number of rotations)
-        for (int c0 = 0; c0 < ng; c0 += 15) {
-            const int c1 = ng < c0 + 15 ? ng : c0 + 15;
-            for (int g = c0; g < c1; g += 3) {
-                stage(G0, G1, G2, g);
-                if (g + 1 >= c1) break;
-                stage(G1, G2, G0, g + 1);
-                if (g + 2 >= c1) break;
-                stage(G2, G0, G1, g + 2);
-            }
-            ed += static_cast<double>(eb);
-            eb = 0.f;
-        }
-        if (w + 1 < nwin) win_store<ROWS16>(a, lds, buf ^ 1, tab2 + (buf ^ 1) * L.tab_elems, 8, bad, addf, cm);
-        lds_barrier();
-    };
-    for (int w = 0; w < nwin; w += 2) {
-        forward_window(w, s0, s1);
-        if (w + 1 < nwin) forward_window(w + 1, s1, s0);
-    }
-    // chains' makespans and energies -> the candidate's (chain order)
-    double *esum = reinterpret_cast<double *>(lds + L.off_x);
-    float *tsum = reinterpret_cast<float *>(lds + L.off_x + 8 * 64 * kWinMaxWaves);
-    esum[wv * 64 + lane] = ed;
-    tsum[wv * 64 + lane] = f;
-    lds_barrier();
-    if (ch == 0) {
-        float T = c.t_const;
-        double e = 0.0;
-        for (int j = 0; j < nc; ++j) {
-            T = fmaxf(T, tsum[(grp * nc + j) * 64 + lane]);
-            e += esum[(grp * nc + j) * 64 + lane];
-        }
-        float E = static_cast<float>(e + static_cast<double>(g.static_power) * static_cast<double>(T));
-        if (bad[cl]) {
-            T = __builtin_nanf("");
-            E = __builtin_nanf("");
-        }
-        tfin[cl] = T;
-        if (gc < B) {
-            To[gc] = T;
-            Eo[gc] = E;
-        }
-    }
-    if (!SLACK) return;
-    lds_barrier();
-
-    const int prlog = a.wlog - 2;                           // float4 pieces per tile row: W / 4
-    // slack tile of window w -> pack order; a wave covers 4 candidates x 16 pieces when rows
-    // are long enough (conflict-free LDS reads with the odd row pitch), else whole rows
-    // (W is a power of two: shifts, no divisions)
-    auto flush_tile = [&](int w) {
-        if (!ROWS16 && (P & 3) != 0) {
-            // rows of a pack count that is not a multiple of 4 (4-byte aligned only): one float
-            // per lane, consecutive lanes on consecutive columns of a row (256-byte pieces)
-            const int n1 = a.NC << a.wlog;
-            for (int q = t; q < n1; q += nt) {
-                const int r = q >> a.wlog, cc = q & (W - 1);
-                const int64_t row = base + r;
-                const int64_t col = (static_cast<int64_t>(w) << a.wlog) + cc;
-                const float v = tfin[r] != tfin[r] ? __builtin_nanf("") : tile[r * (W + 1) + cc];
-                if (row < B && col < P) S[row * P + col] = v;
-            }
-            return;
-        }
-        const int n = a.NC << prlog;
-        for (int q = t; q < n; q += nt) {
-            int r, kk;
-            if (prlog >= 4) {
-                const int j = q & 63, blk = q >> 6, kblog = prlog - 4;
-                const int rg = blk >> kblog, kb = blk & ((1 << kblog) - 1);
-                r = rg * 4 + (j >> 4);
-                kk = kb * 16 + (j & 15);
-            } else {
-                r = q >> prlog;
-                kk = q & ((1 << prlog) - 1);
-            }
-            const float *src = tile + r * (W + 1) + 4 * kk;
-            float4 v = make_float4(src[0], src[1], src[2], src[3]);
-            if (tfin[r] != tfin[r]) v = make_float4(__builtin_nanf(""), __builtin_nanf(""),
-                                                   __builtin_nanf(""), __builtin_nanf(""));
-            const int64_t row = base + r;
-            const int64_t col = (static_cast<int64_t>(w) << a.wlog) + 4 * kk;
-            if (row < B && col < P) *reinterpret_cast<float4 *>(S + row * P + col) = v;   // 16-byte aligned
-        }
-    };
-    for (int i = t; i < F; i += nt) {
-        tabt[W * F + i] = 0.f;
-        tabt[L.tab_elems + W * F + i] = 0.f;
-    }
-
-    // ---------------------------------------------------------------- second forward pass
-    // slack_i = K - D_i with K = T - Tot and D_i = max(D_{i-1}, cst_i - Pre_{i-1}), D_0 = 0
-    // (a candidate with a bad level, K = NaN, gets its NaN row from the flush instead)
-    const float Kc = tfin[cl] - pre;
-    const float K = Kc == Kc ? Kc : 0.f;
-    float D = 0.f, Pr = 0.f;
-    win_load<ROWS16>(a, levels, g.tabt, 4, blocks, base, B, P, 0, s0);
-    win_load<ROWS16>(a, levels, g.tabt, 4, blocks, base, B, P, nwin > 1 ? 1 : 0, s1);
-    win_store<ROWS16>(a, lds, 0, tabt, 4, nullptr, addf, s0);
-    lds_barrier();
-    float *trow = tile + cl * (W + 1);
-    auto scan_window = [&](int w, WinSet &ld, WinSet &cm) {
-        const int buf = w & 1;
-        win_load<ROWS16>(a, levels, g.tabt, 4, blocks, base, B, P, w + 2 < nwin ? w + 2 : nwin - 1, ld);
-        const uint8_t *lrow = lvl0 + buf * L.lvl_buf + cl * L.lvl_pitch;
-        const char *tb = reinterpret_cast<const char *>(tabt + buf * L.tab_elems);
-        const ChainWinStep *rs = recs(buf);
-        int k0, k1;
-        win_range(a, lds, buf, ch, k0, k1);
-        const int ng = (k1 - k0) >> 2;
-        // group g of 4 steps, pipelined like the forward pass: its times are read while the
-        // next group's level bytes and the records of the group after it are in flight
-        auto stage = [&](WinGroup<FIXED> &A, WinGroup<FIXED> &Bn, WinGroup<FIXED> &C, int g) {
-            float tt[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                tt[i] = *reinterpret_cast<const float *>(tb + (((A.ct[i] >> 16) + A.lv[i]) << 2));
-            Bn.levels(lrow);
-            C.read(rs, k0 + 4 * (g + 2));
-            win_issue_point();
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                // (Pre summed as the forward pass sums it: table time, then fixed duration)
-                D = fmaxf(D, A.cst[i] - Pr);
-                Pr += tt[i];
-                if (FIXED) Pr += A.dur[i];
-                trow[A.ct[i] & 0xffffu] = K - D;
-            }
-        };
-        WinGroup<FIXED> G0, G1, G2;
-        G0.read(rs, k0);
-        G1.read(rs, k0 + 4);
-        G0.levels(lrow);
-        for (int g = 0; g < ng; g += 3) {
-            stage(G0, G1, G2, g);
-            if (g + 1 >= ng) break;
-            stage(G1, G2, G0, g + 1);
-            if (g + 2 >= ng) break;
-            stage(G2, G0, G1, g + 2);
-        }
-        if (w + 1 < nwin) win_store<ROWS16>(a, lds, buf ^ 1, tabt + (buf ^ 1) * L.tab_elems, 4, nullptr, addf, cm);
-        lds_barrier();
-        flush_tile(w);
-        lds_barrier();
-    };
-    for (int w = 0; w < nwin; w += 2) {
-        scan_window(w, s0, s1);
-        if (w + 1 < nwin) scan_window(w + 1, s1, s0);
-    }
-}
-
-// The two-pass chain scan (chains_windowed with slack) for the layouts where every window lies
-// wholly inside the graph (P a multiple of W) and a thread holds at most four pieces of the slack
-// tile: every window copy and every flush follows a per-thread plan fixed for the kernel, so the
-// per-window work is the loads, the LDS stores, the flush stores and the barriers, with no bounds
-// checks, category tests or zeroing.  The walk of each window is that of chains_windowed; a
-// candidate with an invalid level gets its NaN row from the flush plan.
-template <bool FIXED, int NT8>
-__global__ void __launch_bounds__(kChainBlockThreads)
-chains_scan_full(DevGraph g, DevChains c, WinArgs a, const uint4 *__restrict__ blocks,
-                 const uint8_t *__restrict__ levels, int64_t B, float *__restrict__ To,
-                 float *__restrict__ Eo, float *__restrict__ S) {
     extern __shared__ float4 smem[];
     char *lds = reinterpret_cast<char *>(smem);
     const int t = threadIdx.x, nt = blockDim.x;
@@ -1113,13 +898,17 @@ chains_scan_full(DevGraph g, DevChains c, WinArgs a, const uint4 *__restrict__ b
     float *tfin = reinterpret_cast<float *>(lds + L.off_tfin);
     float2 *tab2 = reinterpret_cast<float2 *>(lds + L.off_x);     // forward: [2][W + 1][F]
     float *tabt = reinterpret_cast<float *>(lds + L.off_x);       // second pass: [2][W + 1][F]
-    float *tile = reinterpret_cast<float *>(lds + L.off_tile);    // second pass: [NC][W + 1]
     const uint32_t addf = (0x80u - static_cast<uint32_t>(F)) * 0x01010101u;
     // the bits of a byte that is >= F when F is a power of two
     const uint32_t hib = (F & (F - 1)) == 0 ? (0xffu & ~static_cast<uint32_t>(F - 1)) * 0x01010101u : 0u;
+    const uint32_t lds0 = static_cast<uint32_t>(
+        reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) char *)lds));
+    const uint32_t lrow = static_cast<uint32_t>(cl) * L.lvl_pitch;
+    const int kmax = (a.blk_bytes >> 4) - (a.hdr_words >> 2) - 1;
     auto recs = [&](int buf) {
         return reinterpret_cast<const ChainWinStep *>(lds + L.off_blk + buf * a.blk_bytes + 4 * a.hdr_words);
     };
+    auto window = [&](int w) { return w < nwin ? w : nwin - 1; };
 
     // ------------------------------------------------------------------ forward
     for (int i = t; i < a.NC; i += nt) {
@@ -1132,77 +921,61 @@ chains_scan_full(DevGraph g, DevChains c, WinArgs a, const uint4 *__restrict__ b
         tab2[L.tab_elems + W * F + i] = make_float2(0.f, 0.f);
     }
     const uint32_t spare = L.total;                               // 1 KiB past the layout: spare slots
-    WinPlan plan = win_plan<NT8>(a, 8, rows_left, P, spare);
     uint32_t badbits = 0u;
-    const int64_t nrows = rows_left < a.NC ? rows_left : a.NC;
-    WinBufs bf;
-    bf.lvl = win_rsrc(levels + base * P, static_cast<uint32_t>(nrows * P));
-    bf.tab = win_rsrc(g.tab, static_cast<uint32_t>(static_cast<int64_t>(P) * F * 8));
-    bf.blk = win_rsrc(blocks, static_cast<uint32_t>(static_cast<int64_t>(nwin) * a.blk_bytes));
-    bf.tab_win = W * F * 8;
-    WinSet s0, s1;
-    win_load_full<NT8>(a, plan, bf, 0, s0);
-    win_load_full<NT8>(a, plan, bf, nwin > 1 ? 1 : 0, s1);
-    lds_barrier();
-    win_store_full<NT8>(plan, plan.dst0, lds, &badbits, addf, hib, s0);
-    lds_barrier();
     float f = 0.f, pre = 0.f;
     double ed = 0.0;
-    // window w from buffer buf = w & 1; `ld` takes window w + 2, `cm` holds window w + 1
-    auto forward_window = [&](int w, int buf, WinSet &ld, WinSet &cm) {
-        win_load_full<NT8>(a, plan, bf, w + 2 < nwin ? w + 2 : nwin - 1, ld);
-        const uint8_t *lrow = lvl0 + buf * L.lvl_buf + cl * L.lvl_pitch;
-        const char *tb = reinterpret_cast<const char *>(tab2 + buf * L.tab_elems);
-        const ChainWinStep *rs = recs(buf);
-        int k0, k1;
-        win_range(a, lds, buf, ch, k0, k1);
-        float eb = 0.f;
-        const int ng = (k1 - k0) >> 2;
-        auto stage = [&](WinGroup<FIXED> &A, WinGroup<FIXED> &Bn, WinGroup<FIXED> &C, int gi) {
-            float2 te[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                te[i] = *reinterpret_cast<const float2 *>(tb + (((A.ct[i] >> 16) + A.lv[i]) << 3));
-            Bn.levels(lrow);
-            C.read(rs, k0 + 4 * (gi + 2));
-            win_issue_point();
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                f = fmax_nonneg(f, A.cst[i]) + te[i].x;
-                pre += te[i].x;
-                if (FIXED) {
-                    f += A.dur[i];
-                    pre += A.dur[i];
-                }
-                eb += te[i].y;
-            }
-        };
-        WinGroup<FIXED> G0, G1, G2;
-        G0.read(rs, k0);
-        G1.read(rs, k0 + 4);
-        G0.levels(lrow);
-        // fp32 energy blocks of at most 60 steps (15 groups, a whole number of rotations)
-        for (int c0 = 0; c0 < ng; c0 += 15) {
-            const int c1 = ng < c0 + 15 ? ng : c0 + 15;
-            for (int gi = c0; gi < c1; gi += 3) {
-                stage(G0, G1, G2, gi);
-                if (gi + 1 >= c1) break;
-                stage(G1, G2, G0, gi + 1);
-                if (gi + 2 >= c1) break;
-                stage(G2, G0, G1, gi + 2);
-            }
-            ed += static_cast<double>(eb);
-            eb = 0.f;
-        }
-        // (after the last window: a copy of it into the idle buffer, which nothing reads)
-        win_store_full<NT8>(plan, buf ? plan.dst0 : plan.dst1, lds, &badbits, addf, hib, cm);
+    WinBufs bf;
+    bf.lvl = levels + base * P;
+    bf.blk = win_rsrc(blocks, static_cast<uint32_t>(static_cast<int64_t>(nwin) * a.blk_bytes));
+    {
+        const WinPlan<NL, NT, NB> plan = win_plan<NL, NT, NB>(a, 8, rows_left, P, spare);
+        // (the spare entries behind the table complete its last 16 bytes)
+        bf.tab = win_rsrc(g.tab, static_cast<uint32_t>((static_cast<int64_t>(P) * F * 8 + 15) & ~int64_t{15}));
+        bf.tab_win = W * F * 8;
+        constexpr int kSh = SCALED ? 3 : 0;
+        WinSet<NL + NT + NB> s0, s1;
+        win_load<RAG>(a, plan, bf, 0, nwin, P, s0);
+        if (DEPTH == 2) win_load<RAG>(a, plan, bf, window(1), nwin, P, s1);
         lds_barrier();
-    };
-    for (int w = 0; w < nwin; w += 2) {
-        forward_window(w, 0, s0, s1);
-        if (w + 1 < nwin) forward_window(w + 1, 1, s1, s0);
+        win_store<RAG, kSh>(a, plan, plan.dst0, lds, 0, nwin, P, &badbits, addf, hib, s0);
+        lds_barrier();
+        // window w from buffer buf = w & 1; `ld` takes window w + 2, `cm` holds window w + 1
+        auto forward_window = [&](int w, int buf, WinSet<NL + NT + NB> &ld, WinSet<NL + NT + NB> &cm) {
+            win_load<RAG>(a, plan, bf, window(w + DEPTH), nwin, P, DEPTH == 2 ? ld : cm);
+            int k0, k1;
+            win_range(a, lds, buf, ch, k0, k1);
+            float eb = 0.f;
+            win_walk<FIXED, 3, 3 - kSh, emo_f2>(
+                recs(buf), k0, k1, kmax, lds0 + buf * L.lvl_buf, lds0 + L.off_x + buf * L.tab_elems * 8u, lrow,
+                [&](auto j, const WinChunk<FIXED> &ck, emo_f2 te) {
+                    constexpr int J = decltype(j)::value;
+                    f = fmax_nonneg(f, __uint_as_float(row_bcast<J>(ck.cst))) + te.x;
+                    if (SLACK) pre += te.x;
+                    if (FIXED) {
+                        const float d = __uint_as_float(row_bcast<J>(ck.dur));
+                        f += d;
+                        if (SLACK) pre += d;
+                    }
+                    eb += te.y;
+                },
+                [&](int done) {   // fp32 energy blocks of at most 64 steps
+                    if ((done & 48) == 48) {
+                        ed += static_cast<double>(eb);
+                        eb = 0.f;
+                    }
+                });
+            ed += static_cast<double>(eb);
+            // (after the last window: a copy of it into the idle buffer, which nothing reads)
+            win_store<RAG, kSh>(a, plan, buf ? plan.dst0 : plan.dst1, lds, window(w + 1), nwin, P, &badbits, addf,
+                                hib, cm);
+            lds_barrier();
+        };
+        for (int w = 0; w < nwin; w += 2) {
+            forward_window(w, 0, s0, DEPTH == 2 ? s1 : s0);
+            if (w + 1 < nwin) forward_window(w + 1, 1, DEPTH == 2 ? s1 : s0, s0);
+        }
     }
-    win_mark_bad(a, badbits, bad);
+    win_mark_bad<NL>(a, badbits, bad);
     // chains' makespans and energies -> the candidate's (chain order)
     double *esum = reinterpret_cast<double *>(lds + L.off_x);
     float *tsum = reinterpret_cast<float *>(lds + L.off_x + 8 * 64 * kWinMaxWaves);
@@ -1227,71 +1000,59 @@ chains_scan_full(DevGraph g, DevChains c, WinArgs a, const uint4 *__restrict__ b
             Eo[gc] = E;
         }
     }
-    lds_barrier();
-
-    // ---------------------------------------------------------------- second forward pass
-    // slack_i = K - D_i with K = T - Tot and D_i = max(D_{i-1}, cst_i - Pre_{i-1}) (see
-    // chains_windowed); a candidate with an invalid level (K = NaN) gets NaN from the flush
-    const FlushPlan fp = flush_plan(a, rows_left, P, tfin);
-    const __amdgpu_buffer_rsrc_t srows = win_rsrc(S + base * P, static_cast<uint32_t>(nrows * P * 4));
-    plan = win_plan<1>(a, 4, rows_left, P, spare);
-    bf.tab = win_rsrc(g.tabt, static_cast<uint32_t>(static_cast<int64_t>(P) * F * 4));
-    bf.tab_win = W * F * 4;
-    for (int i = t; i < F; i += nt) {
-        tabt[W * F + i] = 0.f;
-        tabt[L.tab_elems + W * F + i] = 0.f;
-    }
-    const float Kc = tfin[cl] - pre;
-    const float K = Kc == Kc ? Kc : 0.f;
-    float D = 0.f, Pr = 0.f;
-    win_load_full<1>(a, plan, bf, 0, s0);
-    win_load_full<1>(a, plan, bf, nwin > 1 ? 1 : 0, s1);
-    win_store_full<1>(plan, plan.dst0, lds, nullptr, addf, hib, s0);
-    lds_barrier();
-    float *trow = tile + cl * (W + 1);
-    auto scan_window = [&](int w, int buf, WinSet &ld, WinSet &cm) {
-        win_load_full<1>(a, plan, bf, w + 2 < nwin ? w + 2 : nwin - 1, ld);
-        const uint8_t *lrow = lvl0 + buf * L.lvl_buf + cl * L.lvl_pitch;
-        const char *tb = reinterpret_cast<const char *>(tabt + buf * L.tab_elems);
-        const ChainWinStep *rs = recs(buf);
-        int k0, k1;
-        win_range(a, lds, buf, ch, k0, k1);
-        const int ng = (k1 - k0) >> 2;
-        auto stage = [&](WinGroup<FIXED> &A, WinGroup<FIXED> &Bn, WinGroup<FIXED> &C, int gi) {
-            float tt[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                tt[i] = *reinterpret_cast<const float *>(tb + (((A.ct[i] >> 16) + A.lv[i]) << 2));
-            Bn.levels(lrow);
-            C.read(rs, k0 + 4 * (gi + 2));
-            win_issue_point();
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                D = fmaxf(D, A.cst[i] - Pr);
-                Pr += tt[i];
-                if (FIXED) Pr += A.dur[i];
-                trow[A.ct[i] & 0xffffu] = K - D;
-            }
-        };
-        WinGroup<FIXED> G0, G1, G2;
-        G0.read(rs, k0);
-        G1.read(rs, k0 + 4);
-        G0.levels(lrow);
-        for (int gi = 0; gi < ng; gi += 3) {
-            stage(G0, G1, G2, gi);
-            if (gi + 1 >= ng) break;
-            stage(G1, G2, G0, gi + 1);
-            if (gi + 2 >= ng) break;
-            stage(G2, G0, G1, gi + 2);
+    if constexpr (SLACK) {
+        lds_barrier();
+        // -------------------------------------------------------------- second forward pass
+        // a candidate with an invalid level (K = NaN) gets its NaN row from the flush instead
+        constexpr int NF = 4 * NL;   // float4 pieces of the tile are four times the level pieces
+        const FlushPlan<NF> fp = flush_plan<NF>(a, rows_left, P, tfin);
+        const int64_t nrows = rows_left < a.NC ? rows_left : a.NC;
+        const __amdgpu_buffer_rsrc_t srows = win_rsrc(S + base * P, static_cast<uint32_t>(nrows * P * 4));
+        const WinPlan<NL, 1, NB> plan = win_plan<NL, 1, NB>(a, 4, rows_left, P, spare);
+        bf.tab = win_rsrc(g.tabt, static_cast<uint32_t>((static_cast<int64_t>(P) * F * 4 + 15) & ~int64_t{15}));
+        bf.tab_win = W * F * 4;
+        constexpr int kSh = SCALED ? 2 : 0;
+        for (int i = t; i < F; i += nt) {
+            tabt[W * F + i] = 0.f;
+            tabt[L.tab_elems + W * F + i] = 0.f;
         }
-        win_store_full<1>(plan, buf ? plan.dst0 : plan.dst1, lds, nullptr, addf, hib, cm);
+        const float Kc = tfin[cl] - pre;
+        const float K = Kc == Kc ? Kc : 0.f;
+        float D = 0.f, Pr = 0.f;
+        WinSet<NL + 1 + NB> s0, s1;
+        win_load<RAG>(a, plan, bf, 0, nwin, P, s0);
+        if (DEPTH == 2) win_load<RAG>(a, plan, bf, window(1), nwin, P, s1);
+        win_store<RAG, kSh>(a, plan, plan.dst0, lds, 0, nwin, P, nullptr, addf, hib, s0);
         lds_barrier();
-        flush_full(fp, srows, lds, w, a.wlog);
-        lds_barrier();
-    };
-    for (int w = 0; w < nwin; w += 2) {
-        scan_window(w, 0, s0, s1);
-        if (w + 1 < nwin) scan_window(w + 1, 1, s1, s0);
+        const uint32_t trow = lds0 + L.off_tile + 4u * static_cast<uint32_t>(cl * (W + 1));
+        auto scan_window = [&](int w, int buf, WinSet<NL + 1 + NB> &ld, WinSet<NL + 1 + NB> &cm) {
+            win_load<RAG>(a, plan, bf, window(w + DEPTH), nwin, P, DEPTH == 2 ? ld : cm);
+            int k0, k1;
+            win_range(a, lds, buf, ch, k0, k1);
+            const uint32_t lvl_base = lds0 + static_cast<uint32_t>(buf) * L.lvl_buf;
+            // a chunk's column address times four, plus tr, is its slack's address
+            const uint32_t tr = trow - 4u * lvl_base;
+            win_walk<FIXED, 2, 2 - kSh, float>(
+                recs(buf), k0, k1, kmax, lvl_base, lds0 + L.off_x + buf * L.tab_elems * 4u, lrow,
+                [&](auto j, const WinChunk<FIXED> &ck, float tt) {
+                    constexpr int J = decltype(j)::value;
+                    D = fmaxf(D, __uint_as_float(row_bcast<J>(ck.cst)) - Pr);
+                    Pr += tt;
+                    if (FIXED) Pr += __uint_as_float(row_bcast<J>(ck.dur));
+                    lds_put(row_bcast<J>(4u * ck.col) + tr, K - D);
+                },
+                [](int) {});
+            win_store<RAG, kSh>(a, plan, buf ? plan.dst0 : plan.dst1, lds, window(w + 1), nwin, P, nullptr, addf, hib,
+                                cm);
+            lds_barrier();
+            if (RAG && w == nwin - 1) flush_last(a, srows, lds, tfin, w, rows_left, P);
+            else flush_window<NF>(fp, srows, lds, w, a.wlog);
+            lds_barrier();
+        };
+        for (int w = 0; w < nwin; w += 2) {
+            scan_window(w, 0, s0, DEPTH == 2 ? s1 : s0);
+            if (w + 1 < nwin) scan_window(w + 1, 1, DEPTH == 2 ? s1 : s0, s0);
+        }
     }
 }
 
@@ -1310,17 +1071,34 @@ bool staged_ok(const DevGraph &g, const DevChains &c) {
 size_t round256(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
 }  // namespace
 
-bool chain_window_fits(int32_t nc, int32_t F, int32_t W, int32_t blk_bytes, bool rows16, int32_t *groups) {
+namespace {
+// The slot counts the kernel is compiled for.
+bool slots_compiled(const WinSlots &s) {
+    return s.tab4 <= 1 && ((s.lvl == 1 && s.tab8 == 1 && s.blk <= 2) || (s.lvl == 1 && s.tab8 == 2 && s.blk == 1) ||
+                           (s.lvl == 2 && s.tab8 == 1 && s.blk == 1));
+}
+}  // namespace
+
+bool chain_window_fits(int32_t nc, int32_t F, int32_t W, int32_t blk_bytes, int32_t P, int32_t *groups) {
     if (nc < 1 || nc > kWinMaxWaves || F < 1 || F > 128 || W < 16 || W > 256 || blk_bytes % 16 != 0)
         return false;
-    const int G = kWinMaxWaves / nc;
-    const int NC = 64 * G, nthreads = 64 * G * nc;
-    const WinLayout L = win_layout(W, NC, F, G * nc, blk_bytes);
-    int sl, st8, st4, sb;
-    if (L.total > kWinLds || !win_slots(W, NC, F, blk_bytes, nthreads, &sl, &st8, &st4, &sb)) return false;
-    // rows that are not 16-byte aligned: one level piece per thread (its five dwords are held
-    // from one window to the next)
-    if (!rows16 && sl > 1) return false;
+    // (byte offsets into the table and the step blocks are 32-bit)
+    if ((static_cast<int64_t>(P) + W - 1) / W * blk_bytes >= int64_t{1} << 31) return false;
+    const int top = kWinMaxWaves / nc;
+    const WinLayout L = win_layout(W, 64 * top, F, top * nc, blk_bytes);
+    const WinSlots sl = win_slots(W, 64 * top, F, blk_bytes, 64 * top * nc);
+    if (L.total > kWinLds || !slots_compiled(sl)) return false;
+    // rows that are not 16-byte aligned: one level piece per thread
+    if (P % 16 != 0 && sl.lvl > 1) return false;
+    // Groups of 64 candidates per workgroup.  Workgroups of one group leave the fewest waves waiting at
+    // a barrier and the shortest last round: 2,043 kernels on 6 streams, 100,003 candidates 452 us with one
+    // group, 499 with two; 3,001 on 2 streams 650, 684, and 775 with eight; but each copies the window's
+    // table, so past 16 levels (a table row larger than two groups' level bytes) two share it: 5,000
+    // kernels on 3 streams with 24 levels 796 and 730.  A workgroup's slack rows span less than 2^31
+    // bytes, and the copy has to fit the threads.
+    int G = F <= 16 || top == 1 ? 1 : 2;
+    while (G <= top && !slots_compiled(win_slots(W, 64 * G, F, blk_bytes, 64 * G * nc))) ++G;
+    if (G > top || static_cast<int64_t>(64 * G) * P * 4 >= int64_t{1} << 31) return false;
     *groups = G;
     return true;
 }
@@ -1338,13 +1116,6 @@ bool chains_windowed_ok(const DevChains &c, const uint8_t *levels, const float *
            reinterpret_cast<uintptr_t>(slack) % 16 == 0;
 }
 
-namespace {
-int64_t win_grid(const DevChains &c, int64_t B) {
-    const int64_t NC = 64 * static_cast<int64_t>(c.groups);
-    return (B + NC - 1) / NC;
-}
-}  // namespace
-
 size_t chains_scratch_bytes(const DevGraph &g, const DevChains &c, const uint8_t *levels, int64_t B,
                             const float *slack_ptr) {
     const bool slack = slack_ptr != nullptr;
@@ -1359,10 +1130,18 @@ size_t chains_scratch_bytes(const DevGraph &g, const DevChains &c, const uint8_t
 }
 
 namespace {
-template <bool SLACK, bool FIXED, bool ROWS16>
-hipError_t launch_windowed_kernel(dim3 gd, dim3 bd, size_t lds, hipStream_t s, const DevGraph &g,
-                                  const DevChains &c, const WinArgs &a, const uint8_t *levels, int64_t B,
-                                  float *T, float *E, float *S) {
+struct WinLaunch {
+    dim3 grid, block;
+    size_t lds;
+    hipStream_t stream;
+    const uint8_t *levels;
+    int64_t B;
+    float *T, *E, *S;
+};
+
+template <bool SLACK, bool FIXED, bool RAG, bool SCALED, int NL, int NT, int NB, int DEPTH>
+hipError_t launch_windowed_kernel(const WinLaunch &l, const DevGraph &g, const DevChains &c, const WinArgs &a) {
+    const auto kernel = &chains_windowed<SLACK, FIXED, RAG, SCALED, NL, NT, NB, DEPTH>;
     // the dynamic LDS limit is raised once per device (the caller made the graph's device current)
     static std::atomic<uint64_t> done{0};
     int dev = 0;
@@ -1370,81 +1149,75 @@ hipError_t launch_windowed_kernel(dim3 gd, dim3 bd, size_t lds, hipStream_t s, c
     if (e != hipSuccess) return e;
     const uint64_t bit = dev < 64 ? uint64_t{1} << dev : 0;
     if (!bit || !(done.load(std::memory_order_acquire) & bit)) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(&chains_windowed<SLACK, FIXED, ROWS16>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kWinLds));
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                static_cast<int>(kWinLds + kWinSpare));
         if (e != hipSuccess) return e;
         done.fetch_or(bit, std::memory_order_acq_rel);
     }
-    hipLaunchKernelGGL((chains_windowed<SLACK, FIXED, ROWS16>), gd, bd, lds, s, g, c, a, c.blocks, levels, B, T,
-                       E, S);
+    hipLaunchKernelGGL(kernel, l.grid, l.block, l.lds, l.stream, g, c, a, c.blocks, l.levels, l.B, l.T, l.E, l.S);
     return hipGetLastError();
 }
 
-template <bool FIXED, int NT8>
-hipError_t launch_scan_full_kernel(dim3 gd, dim3 bd, size_t lds, hipStream_t s, const DevGraph &g,
-                                   const DevChains &c, const WinArgs &a, const uint8_t *levels, int64_t B,
-                                   float *T, float *E, float *S) {
-    static std::atomic<uint64_t> done{0};
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    const uint64_t bit = dev < 64 ? uint64_t{1} << dev : 0;
-    if (!bit || !(done.load(std::memory_order_acquire) & bit)) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(&chains_scan_full<FIXED, NT8>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kWinLds + kWinSpare));
-        if (e != hipSuccess) return e;
-        done.fetch_or(bit, std::memory_order_acq_rel);
+template <bool SLACK, bool FIXED, bool RAG, bool SCALED, int DEPTH>
+hipError_t launch_windowed_slots(const WinSlots &sl, const WinLaunch &l, const DevGraph &g, const DevChains &c,
+                                 const WinArgs &a) {
+    if (sl.lvl == 2) return launch_windowed_kernel<SLACK, FIXED, RAG, SCALED, 2, 1, 1, DEPTH>(l, g, c, a);
+    if (sl.tab8 == 2) return launch_windowed_kernel<SLACK, FIXED, RAG, SCALED, 1, 2, 1, DEPTH>(l, g, c, a);
+    if (sl.blk == 2) return launch_windowed_kernel<SLACK, FIXED, RAG, SCALED, 1, 1, 2, DEPTH>(l, g, c, a);
+    return launch_windowed_kernel<SLACK, FIXED, RAG, SCALED, 1, 1, 1, DEPTH>(l, g, c, a);
+}
+
+// Copies two windows ahead where the waves of one workgroup are all that a compute unit holds (more
+// than 12 chains: two workgroups would be more than the 24 waves that 80 registers allow): 65,536
+// kernels on 16 streams 1,600 us against 1,618 with one window ahead, 7,000 kernels (24 levels) 498
+// against 520.  With fewer chains several workgroups cover for each other, and the registers of the
+// second window cost one of them: 8,192 kernels on 12 streams 500 us two ahead, 416 one ahead, 4,097 on 9
+// streams 758 and 670.
+template <bool SLACK, bool RAG>
+hipError_t launch_windowed_depth(const WinSlots &sl, const WinLaunch &l, const DevGraph &g, const DevChains &c,
+                                 const WinArgs &a) {
+    if (g.F <= 32) {
+        if (c.fixed) return launch_windowed_slots<SLACK, true, RAG, true, 1>(sl, l, g, c, a);
+        return a.nc > 12 ? launch_windowed_slots<SLACK, false, RAG, true, 2>(sl, l, g, c, a)
+                         : launch_windowed_slots<SLACK, false, RAG, true, 1>(sl, l, g, c, a);
     }
-    hipLaunchKernelGGL((chains_scan_full<FIXED, NT8>), gd, bd, lds + kWinSpare, s, g, c, a, c.blocks, levels, B, T,
-                       E, S);
-    return hipGetLastError();
+    return c.fixed ? launch_windowed_slots<SLACK, true, RAG, false, 1>(sl, l, g, c, a)
+                   : launch_windowed_slots<SLACK, false, RAG, false, 1>(sl, l, g, c, a);
 }
 
 hipError_t launch_windowed(const DevGraph &g, const DevChains &c, const uint8_t *levels, int64_t B,
                            float *T, float *E, float *slack, const SelTargets &tg, void *scratch,
                            hipStream_t s) {
+    const int G = c.groups;
     WinArgs a;
     a.W = c.win;
     a.wlog = 0;
     while ((1 << a.wlog) < a.W) ++a.wlog;
     a.nc = c.nc;
-    a.NC = 64 * c.groups;
+    a.NC = 64 * G;
     a.F = g.F;
     a.blk_bytes = c.blk_bytes;
     a.hdr_words = c.hdr_words;
-    win_slots(a.W, a.NC, a.F, a.blk_bytes, 64 * c.groups * c.nc, &a.slots_lvl, &a.slots_tab8, &a.slots_tab4,
-              &a.slots_blk);
-    a.L = win_layout(a.W, a.NC, a.F, c.groups * c.nc, c.blk_bytes);
-    const int64_t grid = win_grid(c, B);
+    a.L = win_layout(a.W, a.NC, a.F, G * c.nc, c.blk_bytes);
+    const WinSlots sl = win_slots(a.W, a.NC, a.F, a.blk_bytes, a.NC * c.nc);
     char *p = static_cast<char *>(scratch);
     const size_t vec = round256(static_cast<size_t>(B) * sizeof(float));
-    float *Ts = T ? T : reinterpret_cast<float *>(p);
-    float *Es = E ? E : reinterpret_cast<float *>(p + vec);
-    const dim3 gd(static_cast<unsigned>(grid)), bd(static_cast<unsigned>(64 * c.groups * c.nc));
-    const size_t lds = a.L.total;
-    hipError_t e;
-#define EMO_WIN_ARGS gd, bd, lds, s, g, c, a, levels, B, Ts, Es, slack
-    if (slack && c.full) {
-        // one or two 16-byte forward table pieces per thread (c.full guarantees the rest of the
-        // slot layout: one level piece, one block piece, one second-pass table piece)
-        const bool two = a.slots_tab8 == 2;
-        e = c.fixed ? (two ? launch_scan_full_kernel<true, 2>(gd, bd, lds, s, g, c, a, levels, B, Ts, Es, slack)
-                           : launch_scan_full_kernel<true, 1>(gd, bd, lds, s, g, c, a, levels, B, Ts, Es, slack))
-                    : (two ? launch_scan_full_kernel<false, 2>(gd, bd, lds, s, g, c, a, levels, B, Ts, Es, slack)
-                           : launch_scan_full_kernel<false, 1>(gd, bd, lds, s, g, c, a, levels, B, Ts, Es, slack));
-    } else if (g.P % 16 == 0) {
-        e = slack ? (c.fixed ? launch_windowed_kernel<true, true, true>(EMO_WIN_ARGS)
-                             : launch_windowed_kernel<true, false, true>(EMO_WIN_ARGS))
-                  : (c.fixed ? launch_windowed_kernel<false, true, true>(EMO_WIN_ARGS)
-                             : launch_windowed_kernel<false, false, true>(EMO_WIN_ARGS));
-    } else {
-        e = slack ? (c.fixed ? launch_windowed_kernel<true, true, false>(EMO_WIN_ARGS)
-                             : launch_windowed_kernel<true, false, false>(EMO_WIN_ARGS))
-                  : (c.fixed ? launch_windowed_kernel<false, true, false>(EMO_WIN_ARGS)
-                             : launch_windowed_kernel<false, false, false>(EMO_WIN_ARGS));
-    }
-#undef EMO_WIN_ARGS
-    if (e == hipSuccess && tg.n) e = launch_select_results(Ts, Es, B, tg, s);
+    WinLaunch l;
+    l.T = T ? T : reinterpret_cast<float *>(p);
+    l.E = E ? E : reinterpret_cast<float *>(p + vec);
+    l.S = slack;
+    l.levels = levels;
+    l.B = B;
+    l.grid = dim3(static_cast<unsigned>((B + a.NC - 1) / a.NC));
+    l.block = dim3(static_cast<unsigned>(a.NC * c.nc));
+    l.lds = a.L.total + kWinSpare;
+    l.stream = s;
+    const bool rag = g.P % a.W != 0;
+    hipError_t e = slack ? (rag ? launch_windowed_depth<true, true>(sl, l, g, c, a)
+                                : launch_windowed_depth<true, false>(sl, l, g, c, a))
+                         : (rag ? launch_windowed_depth<false, true>(sl, l, g, c, a)
+                                : launch_windowed_depth<false, false>(sl, l, g, c, a));
+    if (e == hipSuccess && tg.n) e = launch_select_results(l.T, l.E, B, tg, s);
     return e;
 }
 }  // namespace

@@ -657,8 +657,7 @@ bool build_chain_windows(const emo_graph_s &g, const Schedule &sc,
                          const std::vector<std::vector<int32_t>> &chains,
                          std::vector<uint4> *blocks, emo::DevChains *dc) {
     const int32_t nc = static_cast<int32_t>(chains.size());
-    // (level offsets within a workgroup's rows are 32-bit: at most 1024 rows of P bytes; rows of
-    // a pack count that is not a multiple of 16 are copied from the dwords around each piece)
+    // (level offsets within a workgroup's rows are 32-bit: at most 1024 rows of P bytes)
     if (nc < 1 || nc > 16 || g.P < 16 || g.P >= (1 << 21)) return false;
     const int32_t hdr_words = (nc + 1 + 3) / 4 * 4;
     for (int32_t W = 256; W >= 16; W >>= 1) {
@@ -684,8 +683,8 @@ bool build_chain_windows(const emo_graph_s &g, const Schedule &sc,
             }
         }
         if (!monotone) return false;   // narrower windows would not be monotone either
-        // records per window: 8 no-op steps on each side (reads run up to two groups of 4 past
-        // a chain's range) and each chain's steps padded to a multiple of 4
+        // records per window: 8 no-op steps on each side (reads past the last one repeat it) and each
+        // chain's steps padded to a multiple of 4
         std::vector<int32_t> per(static_cast<size_t>(nwin) * nc, 0);
         for (int32_t c = 0; c < nc; ++c)
             for (int32_t w : win[c]) ++per[static_cast<size_t>(w) * nc + c];
@@ -697,7 +696,7 @@ bool build_chain_windows(const emo_graph_s &g, const Schedule &sc,
         }
         const int32_t blk_bytes = 4 * hdr_words + 16 * rec_max;
         int32_t G = 0;
-        if (!emo::chain_window_fits(nc, g.F, W, blk_bytes, g.P % 16 == 0, &G)) continue;
+        if (!emo::chain_window_fits(nc, g.F, W, blk_bytes, g.P, &G)) continue;
         const size_t words = static_cast<size_t>(blk_bytes) / 4;
         emo::ChainWinStep noop;
         noop.ct = static_cast<uint32_t>(W) | (static_cast<uint32_t>(W * g.F) << 16);
@@ -740,21 +739,8 @@ bool build_chain_windows(const emo_graph_s &g, const Schedule &sc,
         dc->fixed = fixed;
         dc->hdr_words = hdr_words;
         dc->blk_bytes = blk_bytes;
-        // per-thread plans of chains_scan_full: NC = 64 G candidates, 64 G nc threads and
-        // NC * W / 4 float4 pieces of the slack tile per window
-        // (and the copy slots that kernel is compiled for: one level piece, one or two forward
-        // and one second-pass table pieces and one step-block piece per thread)
-        const int64_t NC = 64 * static_cast<int64_t>(G);
-        const int64_t nthr = 64 * static_cast<int64_t>(G) * nc;
-        const int64_t tab8 = (static_cast<int64_t>(W) * g.F / 2 + nthr - 1) / nthr;
-        const int64_t tab4 = (static_cast<int64_t>(W) * g.F / 4 + nthr - 1) / nthr;
-        const bool slots = NC * (W / 16) <= nthr && (tab8 == 1 || tab8 == 2) && tab4 == 1 && blk_bytes / 16 <= nthr;
-        dc->full = slots && g.P % W == 0 && NC * W / 4 <= 4 * nthr &&
-                           NC * g.P * 4 < (int64_t(1) << 31) &&
-                           static_cast<int64_t>(g.P) * g.F * 8 < (int64_t(1) << 31) &&
-                           static_cast<int64_t>(nwin) * blk_bytes < (int64_t(1) << 31)
-                       ? 1
-                       : 0;
+        // (reported: every window wholly inside the graph and one level piece per thread)
+        dc->full = g.P % W == 0 && W <= 16 * nc ? 1 : 0;
         return true;
     }
     return false;

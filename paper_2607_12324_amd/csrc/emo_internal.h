@@ -188,22 +188,20 @@ struct DevChains {
     int32_t hdr_words = 0;            // nc + 1 rounded up to a multiple of 4
     int32_t blk_bytes = 0;
     const uint4 *blocks = nullptr;    // [nwin][blk_bytes / 16]
-    // every window lies wholly inside the graph (P a multiple of win), a thread of the windowed
-    // kernel holds at most four float4 pieces of the slack tile, and a workgroup's slack rows
-    // span less than 2^32 bytes: the second-pass kernel with per-thread copy plans applies
+    // every window lies wholly inside the graph (P a multiple of win) and a thread copies one level
+    // piece per window (reported: last_kernels 8 instead of 6)
     int32_t full = 0;
 };
-// Whether the windowed kernel's LDS working set and prefetch fit for `nc` chains, F levels,
-// windows of W packs and step blocks of blk_bytes (rows16: P is a multiple of 16); sets the
-// candidate groups per workgroup.
-bool chain_window_fits(int32_t nc, int32_t F, int32_t W, int32_t blk_bytes, bool rows16, int32_t *groups);
+// Whether the windowed kernel's LDS working set and copies fit for `nc` chains, F levels, P packs in
+// windows of W and step blocks of blk_bytes; sets the candidate groups per workgroup.
+bool chain_window_fits(int32_t nc, int32_t F, int32_t W, int32_t blk_bytes, int32_t P, int32_t *groups);
 // Whether a call runs the windowed kernel (the layout exists and the buffers are 16-byte
 // aligned).
 bool chains_windowed_ok(const DevChains &c, const uint8_t *levels, const float *slack);
 // Whether a call runs the windowed kernel with slack from a second forward pass (a call with
 // slack on the windowed layout, buffers 16-byte aligned).
 bool chains_scan_ok(const DevChains &c, const uint8_t *levels, const float *slack);
-// Whether that call runs the second-pass kernel with per-thread copy plans (chains_scan_full).
+// Whether that call is reported as last_kernels 8 (DevChains.full).
 bool chains_scan_full_ok(const DevChains &c, const uint8_t *levels, const float *slack);
 // Scratch of launch_chains: backward checkpoints and chain-ordered slack (slack only), and
 // makespan/energy buffers.

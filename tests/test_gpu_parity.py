@@ -836,6 +836,39 @@ def skewed_chains(seed, P, S, F, share):
                        np.asarray(pack, np.int32), np.asarray(dur, np.float32), P, F, t, e, 0.3)
 
 
+@pytest.mark.parametrize("case", [(8193, 16, 16, 65), (8207, 13, 32, 64), (8705, 2, 40, 1), (8195, 1, 33, 130),
+                                  (8255, 6, 5, 129), (8256, 11, 24, 63), (8224, 12, 128, 64), (8704, 3, 17, 200)],
+                         ids=lambda c: "x".join(map(str, c)))
+def test_chain_window_edges(torch, emo, case):
+    """Windowed chain kernel at the edges of its copies: last windows of 1, 15, 31 and 63 columns, rows
+    starting at every byte, levels past the byte scaling's limit (33, 40, 128), one and two candidate
+    groups, one and two level pieces, copies one (up to 12 chains) and two windows ahead, and batches
+    around 64 rows; an invalid level in the last column.  On the exact-sum grid makespan and slack equal
+    the oracle's; energies are within the derived bound of fp32 block sums."""
+    P, S_, F, B = case
+    g = synth.stream_graph(sum(case), P, S_, F)
+    rng = np.random.default_rng(P + F)
+    rows = pins.random_rows(rng, g, B)
+    if B > 1:
+        rows[B // 2, P - 1] = F
+    print(f"[case] chain window edges {case}", flush=True)
+    gh = emo.EmoGraph(g, device=0)
+    info = gh.info()
+    assert info["chain_window"] > 0 and info["exact_time_sums"] == 1
+    lv = dev(torch, rows)
+    T, E = gh.eval_policies(lv)
+    assert gh.info()["last_kernels"] == 4, gh.info()
+    T2 = torch.empty_like(T)
+    E2 = torch.empty_like(E)
+    S = gh.slack(lv, makespan=T2, energy=E2)
+    torch.cuda.synchronize()
+    assert gh.info()["last_kernels"] == (8 if info["chain_scan_full"] else 6), gh.info()
+    T_or, E_or, S_or = oracle.slack_batch(g, rows, nthreads=8)
+    parity.assert_eval(host(T), host(E), T_or, E_or, True, f"window edges {case}")
+    parity.assert_eval(host(T2), host(E2), T_or, E_or, True, f"window edges {case} with slack")
+    parity.assert_slack(host(S), S_or, T_or, True, f"window edges {case} slack")
+
+
 def test_chain_scan_long_window_lists(torch, emo):
     """Two-pass scan kernel where one chain holds about 230 steps of a 256-pack window (records
     loaded 64 at a time), with an invalid level and a ragged batch, against the oracle."""
