@@ -1533,7 +1533,9 @@ emo_status evaluate(emo_graph_t g, const uint8_t *levels, int64_t B, float *make
                             : path == Path::kChainLanes ? emo::select_results_blocks(B)
                                                    : emo::forward_blocks(B);
     const emo::DevProgram &prog = per_node ? g->dg.slack_node : g->dg.slack_pack;
-    size_t part_bytes = results ? static_cast<size_t>(tg.n) * nblocks * emo::kPartialBytes : 0;
+    // (one group: its workgroup writes the selections, with no records and no second launch)
+    const bool direct = results && nblocks == 1 && path != Path::kChainLanes;
+    size_t part_bytes = results && !direct ? static_cast<size_t>(tg.n) * nblocks * emo::kPartialBytes : 0;
     part_bytes = (part_bytes + 255) & ~static_cast<size_t>(255);
     size_t work_bytes = 0;
     if (path == Path::kChain) work_bytes = emo::chain_scratch_bytes(g->jc.plan, B);
@@ -1551,8 +1553,8 @@ emo_status evaluate(emo_graph_t g, const uint8_t *levels, int64_t B, float *make
                         hipGetErrorString(ea));
         }
     }
-    tg.part = results ? scratch : nullptr;
-    tg.nparts = nblocks;
+    tg.part = direct ? results : results ? scratch : nullptr;
+    tg.nparts = direct ? 0 : nblocks;
     void *work = scratch ? static_cast<char *>(scratch) + part_bytes : nullptr;
     g->info.last_kernels = path == Path::kChainLanes && emo::chains_scan_full_ok(g->chains, levels, slack)
                                ? 8
@@ -1585,7 +1587,7 @@ emo_status evaluate(emo_graph_t g, const uint8_t *levels, int64_t B, float *make
         }
     }
     if (e == hipSuccess && g->ev_end) e = hipEventRecord(g->ev_end, st);
-    if (results && e == hipSuccess) e = emo::launch_select_finalize(tg, results, st);
+    if (results && !direct && e == hipSuccess) e = emo::launch_select_finalize(tg, results, st);
     if (scratch) {
         hipError_t er = arena_release(g->arena, st);
         if (e == hipSuccess) e = er;
@@ -1697,7 +1699,8 @@ emo_status emo_eval_intervals(emo_graph_t g, const uint8_t *levels, int64_t B, i
         iv_cap = ivk->cap;
     }
     const int64_t nblocks = use_jit ? emo::jit_blocks(ivk->m, B) : emo::forward_blocks(B);
-    size_t part_bytes = result ? static_cast<size_t>(nblocks) * emo::kPartialBytes : 0;
+    const bool direct = result && nblocks == 1;   // (as in evaluate)
+    size_t part_bytes = result && !direct ? static_cast<size_t>(nblocks) * emo::kPartialBytes : 0;
     part_bytes = (part_bytes + 255) & ~static_cast<size_t>(255);
     const size_t work_bytes = use_jit ? 0 : emo::forward_scratch_bytes(g->dg.eval, B);
     std::lock_guard<std::mutex> lock(g->arena.mu);
@@ -1710,8 +1713,8 @@ emo_status emo_eval_intervals(emo_graph_t g, const uint8_t *levels, int64_t B, i
                         hipGetErrorString(ea));
         }
     }
-    tg.part = result ? scratch : nullptr;
-    tg.nparts = nblocks;
+    tg.part = direct ? result : result ? scratch : nullptr;
+    tg.nparts = direct ? 0 : nblocks;
     void *work = scratch ? static_cast<char *>(scratch) + part_bytes : nullptr;
     g->info.last_kernels = use_jit ? 7 : 0;
     hipError_t e = g->ev_begin ? hipEventRecord(g->ev_begin, st) : hipSuccess;
@@ -1720,7 +1723,7 @@ emo_status emo_eval_intervals(emo_graph_t g, const uint8_t *levels, int64_t B, i
     else if (e == hipSuccess)
         e = emo::launch_intervals(g->dg, pol, levels, B, makespan, energy, tg, work, st);
     if (e == hipSuccess && g->ev_end) e = hipEventRecord(g->ev_end, st);
-    if (result && e == hipSuccess) e = emo::launch_select_finalize(tg, result, st);
+    if (result && !direct && e == hipSuccess) e = emo::launch_select_finalize(tg, result, st);
     if (scratch) {
         hipError_t er = arena_release(g->arena, st);
         if (e == hipSuccess) e = er;

@@ -79,8 +79,9 @@ constexpr size_t kPartialBytes = 16;
 
 // The latency targets of one evaluation, passed to the kernels by value (the layout of the
 // kernels' EmoTargets): target k's feasibility mask to mask[k] (when not NULL) and its partial
-// records to part + k * nparts * kPartialBytes (all targets, when part is not NULL).  n = 0: no
-// mask and no selection.
+// records to part + k * nparts * kPartialBytes (all targets, when part is not NULL); nparts 0: the
+// batch is one group of the evaluating kernel, and part is the emo_selection records themselves.
+// n = 0: no mask and no selection.
 constexpr int kMaxTargets = 8;
 struct SelTargets {
     int32_t n = 0;

@@ -10,6 +10,9 @@
 //      of feasible candidates and the makespan of the candidate holding that key;
 //   2. one workgroup reduces the partial records and writes the emo_selection record (a kernel
 //      of the precompiled library, launched after the evaluating kernel).
+// A batch of one group needs no second stage: its workgroup writes the emo_selection record itself
+// (EmoTargets.nparts 0).  A launch costs the calling thread about 3 us: one query of a 64-pack graph
+// took 6.6 us in the library with two launches.
 // The key of a feasible candidate c is (fp32 bits of its energy) << 32 | c.  Energies are
 // >= 0, so the bit pattern orders like the value and equal energies order by index; an
 // infeasible candidate has the key ~0.
@@ -54,9 +57,10 @@ __device__ __forceinline__ void emo_wave_min_key(unsigned long long *key, float 
 
 // Stage 1 for the workgroup's current group of EMO_BLOCK consecutive candidates (group index
 // `group`, candidates group * EMO_BLOCK + threadIdx.x).  Must be called by every thread of the
-// workgroup.  `part` (one record per group) and `mask` may be NULL.
+// workgroup.  `part` (one record per group), `sel` (the batch is this group: the selection itself) and
+// `mask` may be NULL.
 __device__ void emo_select_block(long long group, bool active, float T, float E, long long c,
-                                 long long B, float target, unsigned int *mask, EmoPartial *part) {
+                                 long long B, float target, unsigned int *mask, EmoPartial *part, EmoSel *sel) {
     __shared__ unsigned long long s_key[EMO_WAVES_PER_BLOCK];
     __shared__ float s_T[EMO_WAVES_PER_BLOCK];
     __shared__ unsigned int s_cnt[EMO_WAVES_PER_BLOCK];
@@ -71,7 +75,7 @@ __device__ void emo_select_block(long long group, bool active, float T, float E,
         EMO_SEL_GLOBAL(unsigned int, mask)[w] = (unsigned int)bal;
         if (w + 1 < nwords) EMO_SEL_GLOBAL(unsigned int, mask)[w + 1] = (unsigned int)(bal >> 32);
     }
-    if (!part) return;
+    if (!part && !sel) return;
     unsigned long long key = feas ? (((unsigned long long)__float_as_uint(E)) << 32) |
                                         (unsigned long long)(unsigned int)c
                                   : ~0ull;
@@ -95,6 +99,15 @@ __device__ void emo_select_block(long long group, bool active, float T, float E,
             }
             p.count += s_cnt[w];
         }
+        if (sel) {
+            const bool none = p.key == ~0ull;
+            EMO_SEL_GLOBAL(EmoSel, sel)->index = none ? -1ll : (long long)(p.key & 0xffffffffull);
+            EMO_SEL_GLOBAL(EmoSel, sel)->energy =
+                none ? __builtin_nanf("") : __uint_as_float((unsigned int)(p.key >> 32));
+            EMO_SEL_GLOBAL(EmoSel, sel)->makespan = none ? __builtin_nanf("") : p.makespan;
+            EMO_SEL_GLOBAL(EmoSel, sel)->num_feasible = (long long)p.count;
+            return;
+        }
         // one 16-byte store in the record's layout: key (low word first), count, makespan
         const emo_sel_u4 v = {(unsigned int)p.key, (unsigned int)(p.key >> 32), p.count,
                               __float_as_uint(p.makespan)};
@@ -104,7 +117,8 @@ __device__ void emo_select_block(long long group, bool active, float T, float E,
 
 // The latency targets of one evaluation (Eq. 4 at each of them): the feasibility mask of target
 // k goes to mask[k] (when not NULL) and its per-group partial records to part + k * nparts (all
-// targets, when part is not NULL).  n = 0: no mask and no selection.
+// targets, when part is not NULL); nparts 0: the batch is one group, and part is the emo_selection
+// records, one per target.  n = 0: no mask and no selection.
 #define EMO_MAX_TARGETS 8
 struct EmoTargets {
     int n;
@@ -122,8 +136,10 @@ __device__ void emo_select_all(long long group, bool active, float T, float E, l
     for (int k = 0; k < tg.n; ++k) {
         // the previous target's records in LDS have been read before they are overwritten
         if (k > 0 && tg.part) __syncthreads();
+        const bool direct = tg.part && tg.nparts == 0;
         emo_select_block(group, active, T, E, c, B, tg.t[k], tg.mask[k],
-                         tg.part ? tg.part + k * tg.nparts : (EmoPartial *)0);
+                         tg.part && !direct ? tg.part + k * tg.nparts : (EmoPartial *)0,
+                         direct ? (EmoSel *)tg.part + k : (EmoSel *)0);
     }
     // thread 0 has read the last target's per-wave values before any wave of this workgroup
     // goes on (a workgroup that walks several groups writes them again for the next group)

@@ -165,3 +165,36 @@ def test_targets_without_outputs_and_edge_cases(torch, emo):
     with pytest.raises(emo.EmoError) as ei:
         gh.evaluate_targets(lv, [1.0, float("nan")], results=torch.empty((2, 3), dtype=torch.int64, device="cuda"))
     assert ei.value.status == 1
+
+
+@pytest.mark.parametrize("B", [1, 64, 255, 256, 257, 512, 513])
+@pytest.mark.parametrize("case", ["interpreted", "one-kernel", "segmented", "cut", "chain-windows"])
+def test_selection_of_one_group(torch, emo, case, B):
+    """Batches around one workgroup's candidates (256 or 512): within it the evaluating kernel writes the
+    selections itself, past it from partial records.  Every target's record against Eq. 4 on the
+    returned makespans and energies, over a record buffer that held other values, twice."""
+    g = graph_of(case)
+    gh = emo.EmoGraph(g, device=0, kernel_mode=1 if case == "interpreted" else 0)
+    rng = np.random.default_rng(B + len(case))
+    rows = pins.random_rows(rng, g, B)
+    if B > 1:
+        rows[B // 2, 0] = g.num_levels
+    print(f"[case] one group {case} B={B}", flush=True)
+    lv = dev(torch, rows)
+    T, E = gh.eval_policies(lv)
+    Th, Eh = host(T).astype(np.float64), host(E).astype(np.float64)
+    targets = targets_for(Th)
+    for _ in range(2):
+        res = torch.full((len(targets), 3), -7, dtype=torch.int64, device="cuda")
+        masks = [torch.full(((B + 31) // 32,), -1, dtype=torch.int32, device="cuda") for _ in targets]
+        gh.evaluate_targets(lv, targets, makespan=T, energy=E, masks=masks, results=res)
+        torch.cuda.synchronize()
+        for k, t in enumerate(targets):
+            idx, feas, n = oracle.select(Th, Eh, float(np.float32(t)))
+            sel = emo.parse_selection(res[k])
+            assert (sel.index, sel.num_feasible) == (idx, n), (case, B, k, sel)
+            assert np.array_equal(emo.unpack_mask(masks[k], B), feas)
+            if idx >= 0:
+                assert sel.energy == Eh[idx] and sel.makespan == Th[idx]
+            else:
+                assert np.isnan(sel.energy) and np.isnan(sel.makespan)
