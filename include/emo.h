@@ -488,6 +488,12 @@ emo_status emo_pack_model(int32_t num_metrics, int32_t num_benchmarks, const flo
  * EMO_ERR_UNSUPPORTED when the graph is too large for one specialised kernel. */
 emo_status emo_graph_specialized_source(emo_graph_t g, char *buf, int64_t *len);
 
+/* Diagnostics: the HIP source of the per-node slack kernel of `g` (emo_sp_nodes, compiled on the first
+ * call with per-node slack), same buffer convention.  EMO_ERR_UNSUPPORTED when the graph has none: more
+ * than 160 candidate-dependent steps, more than 1,024 nodes, packs out of visiting order or an edge to a
+ * lower node id (the interpreting kernels then run such calls). */
+emo_status emo_graph_node_source(emo_graph_t g, char *buf, int64_t *len);
+
 /* Diagnostics: the HIP source of the segmented specialised kernels of `g`, used for calls
  * without slack on graphs too large for one kernel or whose (time, energy) table exceeds the
  * 64 KB one kernel holds in LDS, and for slack on graphs too large to keep every finish time in

@@ -108,8 +108,6 @@ constexpr int32_t kCutSubPacks = 32;
 // are held in registers (wider graphs keep the interpreting kernels, which spill cold values to
 // device scratch by design).
 constexpr int32_t kChainMaxLive = 48;
-constexpr size_t kJitTableLds = 64 * 1024;
-constexpr size_t kJitTableLdsSlack = 40 * 1024;
 
 // Restores the caller's current device on scope exit.
 struct DeviceGuard {
@@ -643,8 +641,6 @@ void release_device(emo_graph_s *g) {
     g->allocations.clear();
 }
 
-bool is_pow2(int32_t x) { return x > 0 && (x & (x - 1)) == 0; }
-
 // Chain-lane program of a folded schedule whose steps form disjoint chains (at most one
 // candidate-dependent predecessor and successor each) and at most 64 of them: steps[k][lane]
 // is the k-th step of chain `lane`, padded with steps that leave a finish time unchanged.
@@ -910,32 +906,16 @@ bool exact_time_sums(const emo_graph_s &g, const float *pack_time) {
     return emin == INT_MAX || T < std::ldexp(1.0, 24 + emin);
 }
 
-size_t jit_table_bytes(const emo_graph_s &g) {
-    return (static_cast<size_t>(g.P) * g.F + (is_pow2(g.F) ? 0 : emo::kTablePad)) * sizeof(float2);
-}
+size_t jit_table_bytes(const emo_graph_s &g) { return emo::jit_table_bytes(g.jg); }
 
-// Source of the specialised kernels and the workgroup size they are written for.
-std::string jit_source(const emo_graph_s &g, int *block_out) {
-    const size_t tb = jit_table_bytes(g);
-    const bool with_slack = g.jit_slack_eligible;
-    const bool tab_lds = tb <= (with_slack ? kJitTableLdsSlack : kJitTableLds);
-    // one LDS copy of a large table serves a larger workgroup
-    const int block = !tab_lds || tb <= 16 * 1024 ? 256 : (tb <= 32 * 1024 ? 512 : 1024);
-    *block_out = block;
-    return emo::jit_generate(g.jg, with_slack ? emo::JitSlack::kPacks : emo::JitSlack::kNone, tab_lds, block);
-}
-
-// Source of the per-node slack kernel (g.jg.nodes not empty: its table is at most 160 packs' rows).
-std::string node_source(const emo_graph_s &g, int *block_out) {
-    const size_t tb = jit_table_bytes(g);
-    const bool tab_lds = tb <= kJitTableLdsSlack;
-    *block_out = !tab_lds || tb <= 16 * 1024 ? 256 : 512;
-    return emo::jit_generate(g.jg, emo::JitSlack::kNodes, tab_lds, *block_out);
+// What the one-kernel module holds besides emo_sp_select.
+emo::JitSlack jit_slack(const emo_graph_s &g) {
+    return g.jit_slack_eligible ? emo::JitSlack::kPacks : emo::JitSlack::kNone;
 }
 
 size_t iv_table_bytes(const emo_graph_s &g) {
     const size_t tb = static_cast<size_t>(g.P) * g.F * sizeof(float2);
-    return tb <= kJitTableLds ? tb : 0;   // 0: read from device memory
+    return tb <= emo::kJitTableLds ? tb : 0;   // 0: read from device memory
 }
 
 // Generates and compiles the time-interval kernel of `block` candidates a workgroup once; *out is its
@@ -945,7 +925,7 @@ int ensure_iv(emo_graph_s *g, int block, emo_graph_s::IvKernel **out) {
     emo_graph_s::IvKernel &k = g->iv[block == 256 ? 0 : block == 512 ? 1 : 2];
     *out = &k;
     if (k.state != 0) return k.state;
-    const bool tab_lds = static_cast<size_t>(g->P) * g->F * sizeof(float2) <= kJitTableLds;
+    const bool tab_lds = static_cast<size_t>(g->P) * g->F * sizeof(float2) <= emo::kJitTableLds;
     const std::string src = emo::jit_generate_intervals(g->jg, tab_lds, block);
     DeviceGuard guard(g->device);
     emo::JitModule m;
@@ -994,8 +974,7 @@ bool iv_buckets(const float *pts, int K, float *scale_out, int *M_out) {
 int ensure_jit(emo_graph_s *g) {
     std::lock_guard<std::mutex> lock(g->jit_mu);
     if (g->jit_state != 0) return g->jit_state;
-    int block = 256;
-    std::string src = jit_source(*g, &block);
+    const std::string src = emo::jit_generate(g->jg, jit_slack(*g));
     DeviceGuard guard(g->device);
     emo::JitModule m;
     std::string log;
@@ -1005,7 +984,9 @@ int ensure_jit(emo_graph_s *g) {
         g->info.specialized |= 4;
         return -1;
     }
-    m.block = block;
+    const emo::JitLayout lay = emo::jit_layout(g->jg, jit_slack(*g));
+    m.block = lay.block;
+    m.slack_block = lay.slack_block;
     // persistent workgroups pay off when each one copies a large table into LDS
     if (jit_table_bytes(*g) > 16 * 1024) emo::jit_set_caps(&m);
     g->jm = m;
@@ -1019,8 +1000,7 @@ int ensure_jit(emo_graph_s *g) {
 int ensure_nodes(emo_graph_s *g) {
     std::lock_guard<std::mutex> lock(g->jit_mu);
     if (g->node_state != 0) return g->node_state;
-    int block = 256;
-    const std::string src = node_source(*g, &block);
+    const std::string src = emo::jit_generate(g->jg, emo::JitSlack::kNodes);
     DeviceGuard guard(g->device);
     emo::JitModule m;
     std::string log;
@@ -1030,7 +1010,7 @@ int ensure_nodes(emo_graph_s *g) {
         g->info.specialized |= 4;
         return -1;
     }
-    m.block = block;
+    m.slack_block = emo::jit_layout(g->jg, emo::JitSlack::kNodes).slack_block;
     if (jit_table_bytes(*g) > 16 * 1024) emo::jit_set_caps(&m);
     g->jn = m;
     g->node_state = 1;
@@ -1324,7 +1304,7 @@ emo_status emo_load_graph(int32_t num_nodes, int32_t num_edges, const int32_t *e
     // 2^20 candidates and 16 levels, 640 steps on 16 chains (an 80 KB table) take 0.26 ms there
     // against 0.93 ms in one kernel, 2,048 steps 0.82 against 3.84; 512 steps (64 KB, in LDS)
     // take 0.14 ms in one kernel against 0.19.
-    g->chain_eval = narrow && nops <= kChainMaxOps && (nops > kJitMaxOps || jit_table_bytes(*g) > kJitTableLds);
+    g->chain_eval = narrow && nops <= kChainMaxOps && (nops > kJitMaxOps || jit_table_bytes(*g) > emo::kJitTableLds);
     g->chain_slack = narrow && nops > kJitMaxSlackOps && nops <= kChainMaxOps;
     g->chain_scan_first = chains_ok && dc.win > 0 && nops >= kChainScanMinOps;
     g->cut_plan = emo::jit_cut_plan(g->jg, cut_steps(*g, sf), kCutMaxPacks, kCutSubPacks);
@@ -1392,8 +1372,23 @@ emo_status emo_graph_set_timing_events(emo_graph_t g, void *begin_event, void *e
 emo_status emo_graph_specialized_source(emo_graph_t g, char *buf, int64_t *len) {
     if (!g || !len) return fail(EMO_ERR_INVALID_ARGUMENT, "NULL argument");
     if (!g->jit_eligible) return fail(EMO_ERR_UNSUPPORTED, "graph too large for one specialised kernel");
-    int block = 256;
-    std::string src = jit_source(*g, &block);
+    const std::string src = emo::jit_generate(g->jg, jit_slack(*g));
+    const int64_t need = static_cast<int64_t>(src.size()) + 1;
+    if (!buf) {
+        *len = need;
+        return ok();
+    }
+    if (*len < need) return fail(EMO_ERR_INVALID_ARGUMENT, "buffer of %lld bytes, %lld needed",
+                                 (long long)*len, (long long)need);
+    std::memcpy(buf, src.c_str(), static_cast<size_t>(need));
+    *len = need;
+    return ok();
+}
+
+emo_status emo_graph_node_source(emo_graph_t g, char *buf, int64_t *len) {
+    if (!g || !len) return fail(EMO_ERR_INVALID_ARGUMENT, "NULL argument");
+    if (g->jg.nodes.empty()) return fail(EMO_ERR_UNSUPPORTED, "the graph uses no per-node slack kernel");
+    const std::string src = emo::jit_generate(g->jg, emo::JitSlack::kNodes);
     const int64_t need = static_cast<int64_t>(src.size()) + 1;
     if (!buf) {
         *len = need;
@@ -1443,7 +1438,7 @@ emo_status emo_graph_interval_source(emo_graph_t g, char *buf, int64_t *len) {
     if (!g || !len) return fail(EMO_ERR_INVALID_ARGUMENT, "NULL argument");
     if (!g->jit_eligible) return fail(EMO_ERR_UNSUPPORTED, "graph too large for one specialised kernel");
     const size_t tb = static_cast<size_t>(g->P) * g->F * sizeof(float2);
-    const std::string src = emo::jit_generate_intervals(g->jg, tb <= kJitTableLds, 256);
+    const std::string src = emo::jit_generate_intervals(g->jg, tb <= emo::kJitTableLds, 256);
     const int64_t need = static_cast<int64_t>(src.size()) + 1;
     if (!buf) {
         *len = need;
@@ -1526,8 +1521,8 @@ emo_status evaluate(emo_graph_t g, const uint8_t *levels, int64_t B, float *make
     if ((s = choose_path(g, levels, slack, per_node != 0, B, &path)) != EMO_OK) return s;
     DeviceGuard guard(g->device);
     // one selection partial record per block of the evaluating kernel
-    const int64_t nblocks = path == Path::kSingle  ? emo::jit_blocks(g->jm, B)
-                            : path == Path::kNodes ? emo::jit_blocks(g->jn, B)
+    const int64_t nblocks = path == Path::kSingle  ? emo::jit_blocks(g->jm, slack != nullptr, B)
+                            : path == Path::kNodes ? emo::jit_blocks(g->jn, true, B)
                             : path == Path::kChain ? emo::jit_chain_blocks(g->jc, B)
                             : path == Path::kCut   ? emo::jit_cut_blocks(g->jk, B)
                             : path == Path::kChainLanes ? emo::select_results_blocks(B)
@@ -1698,7 +1693,7 @@ emo_status emo_eval_intervals(emo_graph_t g, const uint8_t *levels, int64_t B, i
         }
         iv_cap = ivk->cap;
     }
-    const int64_t nblocks = use_jit ? emo::jit_blocks(ivk->m, B) : emo::forward_blocks(B);
+    const int64_t nblocks = use_jit ? emo::jit_blocks(ivk->m, false, B) : emo::forward_blocks(B);
     const bool direct = result && nblocks == 1;   // (as in evaluate)
     size_t part_bytes = result && !direct ? static_cast<size_t>(nblocks) * emo::kPartialBytes : 0;
     part_bytes = (part_bytes + 255) & ~static_cast<size_t>(255);

@@ -373,9 +373,9 @@ struct JitModule {
     hipFunction_t select = nullptr;  // forward pass with optional outputs and selection
     hipFunction_t slack = nullptr;   // only for graphs small enough to keep every finish time
     double compile_seconds = 0.0;
-    int block = 256;
+    int block = 256, slack_block = 256;   // candidates per workgroup of `select` and `slack`
     // resident workgroups of the one-kernel select / slack kernels on the device (their grid,
-    // at most one workgroup per group of `block` candidates, so each loads the table once)
+    // at most one workgroup per group of candidates, so each loads the table once)
     int64_t select_cap = 0, slack_cap = 0;
     // segmented kernels
     bool chain = false;
@@ -396,7 +396,20 @@ struct JitModule {
 // The one-kernel module: emo_sp_select and, with kPacks, emo_sp_slack; with kNodes emo_sp_nodes alone
 // (the slack of every node, JitGraph.nodes).
 enum class JitSlack { kNone, kPacks, kNodes };
-std::string jit_generate(const JitGraph &g, JitSlack slack, bool tab_lds, int block);
+// Largest tables copied to LDS: by kernels without slack, and by those that stage slack there too.
+constexpr size_t kJitTableLds = 64 * 1024;
+constexpr size_t kJitTableLdsSlack = 40 * 1024;
+// How such a module is laid out: candidates per workgroup of the kernels without and with slack, the table
+// in LDS or read from device memory, slack columns staged at a time in LDS (0: each lane stores its own
+// row).
+struct JitLayout {
+    int block = 256, slack_block = 256;
+    bool tab_lds = false;
+    int kc = 0;
+};
+size_t jit_table_bytes(const JitGraph &g);
+JitLayout jit_layout(const JitGraph &g, JitSlack slack);
+std::string jit_generate(const JitGraph &g, JitSlack slack);
 int jit_compile_nodes(const std::string &src, JitModule *out, std::string *log);   // out->slack
 // Segments of about seg_ops steps (cut where the pack steps so far are a multiple of 64) and
 // recompute sub-segments of at most sub_ops steps.
@@ -425,9 +438,9 @@ hipError_t jit_launch_cut(const JitModule &m, const uint8_t *levels, int64_t B, 
 // 0 on success; otherwise *log holds the compiler's or loader's message.
 int jit_compile(const std::string &src, bool with_slack, JitModule *out, std::string *log);
 void jit_unload(JitModule *m);
-// Candidate groups of the one-kernel specialised kernels for B candidates (one selection
-// partial each).
-int64_t jit_blocks(const JitModule &m, int64_t B);
+// Candidate groups of the one-kernel specialised kernels without or with slack for B candidates (one
+// selection partial each).
+int64_t jit_blocks(const JitModule &m, bool slack, int64_t B);
 // Time-interval kernel specialised to the graph (emo_iv, any K): each workgroup copies its
 // candidates' rows to LDS and looks the start times' intervals up in a bucket table; the batch's
 // change points, idle powers and bucket table parameters by value.

@@ -372,6 +372,8 @@ LevelPlan emit_forward(std::ostringstream &o, const JitGraph &g, std::vector<std
 // spreads each store over 64 rows (2^19 candidates: 24 packs 54 us that way and 14 staged, 35 packs 80
 // and 31, 100 packs 233 and 61).
 int stage_chunk(int cols) { return cols >= 32 ? 32 : (cols + 3) / 4 * 4; }
+constexpr size_t kLdsBytes = 160 * 1024;   // of a compute unit, and a workgroup's limit
+
 // 16-byte stores when rows keep that alignment, else a float per lane.
 bool stage_vec(int cols) { return cols % 4 == 0; }
 
@@ -379,8 +381,8 @@ bool stage_vec(int cols) { return cols % 4 == 0; }
 // Pack durations are read from the table again at an index offset by a zero the compiler cannot
 // see through, so the forward's loads are not kept alive for the whole pass (and the reads stay
 // LDS reads with immediate offsets).
-void emit_backward(std::ostringstream &o, const JitGraph &g, bool staged,
-                   const std::vector<std::string> &level_expr) {
+// kc: columns of a staged piece, 0 when each lane stores its own row.
+void emit_backward(std::ostringstream &o, const JitGraph &g, int kc, const std::vector<std::string> &level_expr) {
     const int n = static_cast<int>(g.ops.size());
     o << "  const float Tb = isbad ? 0.f : T;\n";
     o << "  unsigned int zb = 0u;\n  __asm__ __volatile__(\"\" : \"+v\"(zb));\n";
@@ -407,8 +409,7 @@ void emit_backward(std::ostringstream &o, const JitGraph &g, bool staged,
         if (!op.in.empty()) o << "  const float s" << i << " = lf" << i << " - " << dur << ";\n";
         if (op.pack >= 0) {
             const int p = op.pack;
-            const int kc = stage_chunk(g.P);
-            if (staged) {
+            if (kc > 0) {
                 o << "  stg[" << (p % kc) * 65 << " + lane] = lf" << i << " - f" << i << ";\n";
                 if (p % kc == 0)
                     o << "  emo_flush(stg, stg_bad, S, wbase, B, " << p << ", " << std::min(kc, g.P - p) << ");\n";
@@ -477,9 +478,8 @@ __device__ __forceinline__ void emo_flush(float *stg, const unsigned int *stg_ba
 // isbad and the level words, as emit_backward; columns are node ids.  Bound by the slack stores: 64
 // packs under 64 host nodes, 200,003 candidates, take 31 us with the selection (3.7 TB/s) against 495
 // on the interpreting kernels, which keep every finish time in device memory.
-void emit_backward_nodes(std::ostringstream &o, const JitGraph &g, const std::vector<std::string> &level_expr) {
+void emit_backward_nodes(std::ostringstream &o, const JitGraph &g, int kc, const std::vector<std::string> &level_expr) {
     const int V = static_cast<int>(g.nodes.size());
-    const int kc = stage_chunk(V);
     o << "  const float Tb = isbad ? 0.f : T;\n";
     o << "  unsigned int zb = 0u;\n  __asm__ __volatile__(\"\" : \"+v\"(zb));\n";
     for (int v = V - 1; v >= 0; --v) {
@@ -522,26 +522,51 @@ __device__ __forceinline__ float emo_fmax(float a, float b) {
 
 }  // namespace
 
-std::string jit_generate(const JitGraph &g, JitSlack slack, bool tab_lds, int block) {
+size_t jit_table_bytes(const JitGraph &g) {
+    return (static_cast<size_t>(g.P) * g.F + (is_pow2(g.F) ? 0 : kTablePad)) * sizeof(float2);
+}
+
+JitLayout jit_layout(const JitGraph &g, JitSlack slack) {
+    const size_t tab = jit_table_bytes(g);
+    JitLayout l;
+    l.tab_lds = tab <= (slack == JitSlack::kNone ? kJitTableLds : kJitTableLdsSlack);
+    // one LDS copy of a large table serves a larger workgroup
+    l.block = l.slack_block = !l.tab_lds || tab <= 16 * 1024 ? 256 : tab <= 32 * 1024 ? 512 : 1024;
+    if (slack == JitSlack::kNone || (slack == JitSlack::kPacks && !g.pack_monotone)) return l;
+    l.kc = stage_chunk(slack == JitSlack::kNodes ? static_cast<int>(g.nodes.size()) : g.P);
+    // With slack at most 512: the tiles of 1,024 candidates take 134 KB at 32 columns, more than a table
+    // past 32 KB leaves, and 128 registers a lane do not hold the finish times (2^18 candidates: 130 packs
+    // of 32 levels 80 us, with 1,024 and 16 columns 195; 40 of 128 levels 16 and 20).  Without slack 1,024
+    // copy the table half as often (130 packs of 32 levels 28 us against 33 with 512).
+    l.slack_block = std::min(l.slack_block, 512);
+    return l;
+}
+
+std::string jit_generate(const JitGraph &g, JitSlack slack) {
     const bool with_slack = slack != JitSlack::kNone, nodes = slack == JitSlack::kNodes;
+    const JitLayout lay = jit_layout(g, slack);
+    const bool tab_lds = lay.tab_lds;
     std::ostringstream o;
-    o << "#define EMO_BLOCK " << block << "\n" << kPrelude << kEmoSelectSource << "\n";
+    // (kernels of two sizes: the group size at run time)
+    o << "#define EMO_BLOCK " << (nodes ? lay.slack_block : lay.block) << "\n"
+      << (with_slack && !nodes && lay.slack_block != lay.block ? "#define EMO_GROUP ((int)blockDim.x)\n" : "") << kPrelude
+      << kEmoSelectSource << "\n";
     const long long ntab = static_cast<long long>(g.P) * g.F + (is_pow2(g.F) ? 0 : kTablePad);
     o << "#define NTAB " << ntab << "\n";
     // table access
     if (tab_lds) {
         o << "#define EMO_TABLE_DECL __shared__ float2 tab[NTAB]; \\\n"
-             "  for (int i_ = threadIdx.x; i_ < NTAB; i_ += EMO_BLOCK) tab[i_] = tabg[i_]; \\\n"
+             "  for (int i_ = threadIdx.x; i_ < NTAB; i_ += EMO_GROUP) tab[i_] = tabg[i_]; \\\n"
              "  __syncthreads();\n";
     } else {
         o << "#define EMO_TABLE_DECL const float2 *__restrict__ tab = tabg;\n";
     }
-    // Persistent workgroups: each loads the table once and walks groups of EMO_BLOCK
+    // Persistent workgroups: each loads the table once and walks groups of EMO_GROUP
     // candidates grp = blockIdx.x, blockIdx.x + gridDim.x, ...
     o << "#define EMO_GROUP_LOOP \\\n"
-         "  for (long long grp = blockIdx.x; grp * EMO_BLOCK < B; grp += gridDim.x)\n";
+         "  for (long long grp = blockIdx.x; grp * EMO_GROUP < B; grp += gridDim.x)\n";
     o << "#define EMO_LANE_SETUP \\\n"
-         "  const long long gid = grp * EMO_BLOCK + threadIdx.x; \\\n"
+         "  const long long gid = grp * EMO_GROUP + threadIdx.x; \\\n"
          "  const bool active = gid < B; \\\n"
          "  long long cand = active ? gid : B - 1; \\\n"
          "  (void)active;\n";
@@ -569,13 +594,13 @@ std::string jit_generate(const JitGraph &g, JitSlack slack, bool tab_lds, int bl
          "  }\n}\n";
 
     if (with_slack) {
-        const bool staged = nodes || g.pack_monotone;
+        const bool staged = lay.kc > 0;
         const int cols = nodes ? static_cast<int>(g.nodes.size()) : g.P;
         if (staged) {
-            o << "#define EMO_KC " << stage_chunk(cols) << "\n";
+            o << "#define EMO_KC " << lay.kc << "\n";
             o << flush_source(cols);
         }
-        o << "extern \"C\" __global__ void __launch_bounds__(EMO_BLOCK)\n"
+        o << "extern \"C\" __global__ void __launch_bounds__(" << lay.slack_block << ")\n"
           << (nodes ? "emo_sp_nodes" : "emo_sp_slack") << "(const u8 *__restrict__ lv, long long B, const float2 *__restrict__ tabg,\n"
              "             float *__restrict__ S, float *__restrict__ To, float *__restrict__ Eo,\n"
              "             EmoTargets tg) {\n"
@@ -584,13 +609,14 @@ std::string jit_generate(const JitGraph &g, JitSlack slack, bool tab_lds, int bl
              "  const int wave = threadIdx.x / EMO_WAVE;\n"
              "  (void)lane;\n";
         if (staged) {
-            o << "  __shared__ float stg_all[EMO_WAVES_PER_BLOCK][EMO_KC * 65];\n"
-                 "  __shared__ unsigned int bad_all[EMO_WAVES_PER_BLOCK][EMO_WAVE];\n"
+            const int waves = lay.slack_block / 64;
+            o << "  __shared__ float stg_all[" << waves << "][EMO_KC * 65];\n"
+                 "  __shared__ unsigned int bad_all[" << waves << "][EMO_WAVE];\n"
                  "  float *stg = stg_all[wave];\n"
                  "  unsigned int *stg_bad = bad_all[wave];\n";
         }
         o << "  EMO_GROUP_LOOP {\n  EMO_LANE_SETUP\n"
-             "  const long long wbase = grp * EMO_BLOCK + wave * EMO_WAVE;\n"
+             "  const long long wbase = grp * EMO_GROUP + wave * EMO_WAVE;\n"
              "  (void)wbase;\n";
         o << "  const u8 *__restrict__ row = lv + cand * " << g.P << "LL;\n";
         std::vector<std::string> level_expr(g.ops.size());
@@ -598,8 +624,8 @@ std::string jit_generate(const JitGraph &g, JitSlack slack, bool tab_lds, int bl
         o << "  if (active) { if (To) To[cand] = T; if (Eo) Eo[cand] = E; }\n";
         if (staged) o << "  stg_bad[lane] = isbad ? 1u : 0u;\n";
         lp.launder();
-        if (nodes) emit_backward_nodes(o, g, level_expr);
-        else emit_backward(o, g, staged, level_expr);
+        if (nodes) emit_backward_nodes(o, g, lay.kc, level_expr);
+        else emit_backward(o, g, lay.kc, level_expr);
         o << "  if (tg.n) emo_select_all(grp, active, T, E, cand, B, tg);\n";
         o << "  }\n}\n";
     }
@@ -1757,10 +1783,6 @@ int jit_compile_intervals(const std::string &src, JitModule *out, std::string *l
     return 0;
 }
 
-namespace {
-constexpr size_t kIvLdsPerCu = 160 * 1024;
-}  // namespace
-
 size_t jit_iv_dyn_lds(int block, int K, int M) {
     const size_t sd = static_cast<size_t>(((K + 3) >> 2) | 1);
     return static_cast<size_t>(M) * 8 + static_cast<size_t>(block) * sd * 4;
@@ -1770,7 +1792,7 @@ int jit_iv_block(size_t table_bytes, int K, int M, int64_t B) {
     // waves of a compute unit whose workgroups of `block` candidates share one table copy each
     auto waves = [&](int block) {
         const size_t lds = table_bytes + 4096 + static_cast<size_t>(block) + 512 + jit_iv_dyn_lds(block, K, M);
-        return std::min<int64_t>(16, static_cast<int64_t>(kIvLdsPerCu / lds) * block / 64);
+        return std::min<int64_t>(16, static_cast<int64_t>(kLdsBytes / lds) * block / 64);
     };
     int best = 256;
     for (int block : {512, 1024})
@@ -1778,7 +1800,7 @@ int jit_iv_block(size_t table_bytes, int K, int M, int64_t B) {
     return best;
 }
 
-int64_t jit_blocks(const JitModule &m, int64_t B) { return grid_of(B, m.block); }
+int64_t jit_blocks(const JitModule &m, bool slack, int64_t B) { return grid_of(B, slack ? m.slack_block : m.block); }
 
 namespace {
 int64_t resident_blocks(hipFunction_t f, int block) {
@@ -1800,7 +1822,7 @@ unsigned capped_grid(int64_t B, int block, int64_t cap) {
 
 void jit_set_caps(JitModule *m) {
     m->select_cap = resident_blocks(m->select, m->block);
-    m->slack_cap = resident_blocks(m->slack, m->block);
+    m->slack_cap = resident_blocks(m->slack, m->slack_block);
 }
 
 hipError_t jit_launch_intervals(const JitModule &m, const uint8_t *levels, int64_t B, const float2 *tab,
@@ -1906,7 +1928,7 @@ hipError_t jit_launch_slack(const JitModule &m, const uint8_t *levels, int64_t B
     long long b = B;
     SelTargets dt = tg;
     void *args[] = {&levels, &b, &tab, &S, &T, &E, &dt};
-    return hipModuleLaunchKernel(m.slack, capped_grid(B, m.block, m.slack_cap), 1, 1, m.block, 1, 1, 0,
+    return hipModuleLaunchKernel(m.slack, capped_grid(B, m.slack_block, m.slack_cap), 1, 1, m.slack_block, 1, 1, 0,
                                  s, args, nullptr);
 }
 

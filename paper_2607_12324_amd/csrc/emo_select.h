@@ -5,7 +5,7 @@
 // includes no headers and uses only HIP built-ins.
 //
 // Two stages, with no atomics (thousands of blocks updating one address would serialise):
-//   1. for every group of EMO_BLOCK consecutive candidates, the workgroup that evaluates it
+//   1. for every group of EMO_GROUP consecutive candidates, the workgroup that evaluates it
 //      writes the mask bits of its candidates and one partial record: its least key, its number
 //      of feasible candidates and the makespan of the candidate holding that key;
 //   2. one workgroup reduces the partial records and writes the emo_selection record (a kernel
@@ -20,6 +20,10 @@
 
 #ifndef EMO_BLOCK
 #define EMO_BLOCK 256
+#endif
+// Candidates of a workgroup: EMO_BLOCK, or at most that where kernels of several sizes share a module.
+#ifndef EMO_GROUP
+#define EMO_GROUP EMO_BLOCK
 #endif
 #define EMO_WAVE 64
 #define EMO_WAVES_PER_BLOCK (EMO_BLOCK / EMO_WAVE)
@@ -55,8 +59,8 @@ __device__ __forceinline__ void emo_wave_min_key(unsigned long long *key, float 
     }
 }
 
-// Stage 1 for the workgroup's current group of EMO_BLOCK consecutive candidates (group index
-// `group`, candidates group * EMO_BLOCK + threadIdx.x).  Must be called by every thread of the
+// Stage 1 for the workgroup's current group of EMO_GROUP consecutive candidates (group index
+// `group`, candidates group * EMO_GROUP + threadIdx.x).  Must be called by every thread of the
 // workgroup.  `part` (one record per group), `sel` (the batch is this group: the selection itself) and
 // `mask` may be NULL.
 __device__ void emo_select_block(long long group, bool active, float T, float E, long long c,
@@ -68,7 +72,7 @@ __device__ void emo_select_block(long long group, bool active, float T, float E,
     const unsigned long long bal = __ballot(feas);
     const int lane = threadIdx.x % EMO_WAVE;
     const int wave = threadIdx.x / EMO_WAVE;
-    const long long wbase = group * EMO_BLOCK + wave * EMO_WAVE;
+    const long long wbase = group * EMO_GROUP + wave * EMO_WAVE;
     if (mask && lane == 0 && wbase < B) {
         const long long nwords = (B + 31) / 32;
         const long long w = wbase / 32;
@@ -92,7 +96,7 @@ __device__ void emo_select_block(long long group, bool active, float T, float E,
         p.key = s_key[0];
         p.makespan = s_T[0];
         p.count = s_cnt[0];
-        for (int w = 1; w < EMO_WAVES_PER_BLOCK; ++w) {
+        for (int w = 1; w < EMO_GROUP / EMO_WAVE; ++w) {
             if (s_key[w] < p.key) {
                 p.key = s_key[w];
                 p.makespan = s_T[w];

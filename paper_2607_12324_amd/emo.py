@@ -26,7 +26,7 @@ ENTRY_POINTS = ("emo_load_graph", "emo_free_graph", "emo_graph_get_info",
                 "emo_select_from_results", "emo_select_from_results_noalloc", "emo_dp_search", "emo_eval_intervals",
                 "emo_graph_set_timing_events", "emo_pack_kernels", "emo_contract_packs",
                 "emo_pack_model",
-                "emo_graph_specialized_source",
+                "emo_graph_specialized_source", "emo_graph_node_source",
                 "emo_graph_segmented_source", "emo_graph_cut_source", "emo_graph_interval_source",
                 "emo_status_string",
                 "emo_last_error")
@@ -84,6 +84,7 @@ def _load_library():
         "emo_dp_search": [P, f32, f32, P, i32, P, P, P],
         "emo_eval_intervals": [P, P, i64, i32, P, P, P, P, f32, P, P, P],
         "emo_graph_specialized_source": [P, P, P],
+        "emo_graph_node_source": [P, P, P],
         "emo_graph_segmented_source": [P, P, P],
         "emo_graph_cut_source": [P, P, P],
         "emo_graph_interval_source": [P, P, P],
@@ -213,6 +214,9 @@ class EmoGraph:
 
     def specialized_source(self) -> str:
         return self._source(lib.emo_graph_specialized_source)
+
+    def node_source(self) -> str:
+        return self._source(lib.emo_graph_node_source)
 
     def segmented_source(self) -> str:
         return self._source(lib.emo_graph_segmented_source)

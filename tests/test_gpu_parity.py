@@ -1187,3 +1187,35 @@ def test_one_kernel_slack_rows_of_any_pack_count(torch, emo, P):
                         assert np.array_equal(a[~nan], b[~nan])
         ga.close()
         gi.close()
+
+
+@pytest.mark.parametrize("P,F", [(157, 32), (80, 64), (96, 48), (40, 128), (17, 256)])
+def test_one_kernel_slack_large_tables(torch, emo, P, F):
+    """Tables of 32 to 40 KB, where the table and the staged slack columns share a workgroup's LDS:
+    calls with and without slack run one specialised kernel and give the interpreting kernels' bits."""
+    rng = np.random.default_rng(P * F)
+    g = synth.stream_graph(P, P, 2, F)
+    ga = emo.EmoGraph(g, device=0, kernel_mode=emo.KERNELS_SPECIALIZED)
+    gi = emo.EmoGraph(g, device=0, kernel_mode=emo.KERNELS_INTERPRETED)
+    for B in (1, 1025, 5000):
+        rows = rng.integers(0, F, (B, P)).astype(np.uint8)
+        if B > 2 and F < 256:
+            rows[B // 2, P // 2] = F
+        lv = dev(torch, rows)
+        for per_node in (False, True):
+            print(f"[case] one-kernel slack, large table {g.name} B={B} per_node={per_node}", flush=True)
+            outs = []
+            for gh in (ga, gi):
+                T = torch.empty(B, dtype=torch.float32, device="cuda")
+                E = torch.empty_like(T)
+                S = gh.slack(lv, per_node=per_node, makespan=T, energy=E)
+                assert gh.info()["last_kernels"] == (1 if gh is ga else 0)
+                T2, E2 = gh.eval_policies(lv)
+                assert gh.info()["last_kernels"] == (1 if gh is ga else 0)
+                outs.append([host(x).view(np.uint32) for x in (T, E, S, T2, E2)])
+            for a, b in zip(*outs):
+                nan = np.isnan(b.view(np.float32))
+                assert np.array_equal(nan, np.isnan(a.view(np.float32)))
+                assert np.array_equal(a[~nan], b[~nan])
+    ga.close()
+    gi.close()

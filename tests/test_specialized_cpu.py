@@ -178,6 +178,29 @@ def test_random_graph_kernels_compile(emo, hiprtc, tmp_path, seed):
         check_code_object(path, ["emo_sp_select"])
 
 
+# table sizes around the workgroup sizes' borders (16, 32 and 40 KB), packs a multiple of 32, of 16 or neither
+ONE_KERNEL_TABLES = [(128, 16), (125, 16), (131, 16), (128, 32), (126, 32), (130, 32), (144, 32), (157, 32), (80, 64),
+                     (96, 48), (100, 48), (64, 64), (40, 128), (17, 256), (158, 32), (41, 128)]
+
+
+@pytest.mark.parametrize("P,F", ONE_KERNEL_TABLES)
+def test_one_kernel_slack_layouts_compile(emo, hiprtc, tmp_path, P, F):
+    """Table, staged slack columns and selection arrays fit one workgroup's LDS at every workgroup size:
+    the modules of per-pack and per-node slack compile (a sum past the limit is a compile error)."""
+    table = (P * F + (0 if F & (F - 1) == 0 else 256)) * 8
+    in_lds = table <= 40 * 1024
+    gh = emo.EmoGraph(synth.stream_graph(P, P, 2, F), device=-1)
+    for src, name, cols in ((gh.specialized_source(), "emo_sp_slack", P), (gh.node_source(), "emo_sp_nodes", gh.num_nodes)):
+        kc = int(re.search(r"#define EMO_KC (\d+)", src).group(1))
+        block = int(re.search(r"__launch_bounds__\((\d+)\)\s+" + name, src).group(1))
+        waves = int(re.search(r"float stg_all\[(\d+)\]", src).group(1))
+        assert kc == min(32, (cols + 3) // 4 * 4)
+        assert block == 64 * waves == (256 if not in_lds or table <= 16384 else 512)
+        assert (table if in_lds else 0) + waves * (kc * 65 + 64) * 4 < 160 * 1024 - 512
+        notes = kernel_notes(compile_source(hiprtc, src, tmp_path))
+        assert name in notes and ("emo_sp_select" in notes) == (name == "emo_sp_slack"), notes
+
+
 @pytest.mark.parametrize("k", [1, 2, 3])
 def test_interval_kernels_compile(emo, hiprtc, tmp_path, k):
     """The time-interval kernel of the small workloads (the 512-pack graph's 64 KB table in LDS,
