@@ -370,8 +370,10 @@ LevelPlan emit_forward(std::ostringstream &o, const JitGraph &g, std::vector<std
 // time; with kc = 32 each candidate's piece is one 128-byte line.  The last piece of a row may be
 // shorter, and rows of any column count are staged: a lane that stores its own row a float at a time
 // spreads each store over 64 rows (2^19 candidates: 24 packs 54 us that way and 14 staged, 35 packs 80
-// and 31, 100 packs 233 and 61).
-int stage_chunk(int cols) { return cols >= 32 ? 32 : (cols + 3) / 4 * 4; }
+// and 31, 100 packs 233 and 61).  Rows of an odd multiple of 16 columns leave in pieces of 16: half the
+// tile (2^18 candidates: 144 packs of 16 levels 38 us against 45 with 32 columns, 48 of 24 levels 15.0
+// against 16.3).
+int stage_chunk(int cols) { return cols % 32 == 16 ? 16 : cols >= 32 ? 32 : (cols + 3) / 4 * 4; }
 constexpr size_t kLdsBytes = 160 * 1024;   // of a compute unit, and a workgroup's limit
 
 // 16-byte stores when rows keep that alignment, else a float per lane.
@@ -456,10 +458,11 @@ __device__ __forceinline__ void emo_flush(float *stg, const unsigned int *stg_ba
 )";
     if (either) s += "  } else {\n";
     if (!vec || either)
-        s += R"(  // 32 consecutive lanes cover a candidate's segment
+        s += R"(  // consecutive lanes cover a candidate's segment
+  constexpr int per = EMO_KC > 16 ? 32 : 16;
 #pragma unroll 4
-  for (int m = 0; m < EMO_WAVE / 2; ++m) {
-    const int r = 2 * m + lane / 32, c = lane % 32;
+  for (int m = 0; m < per; ++m) {
+    const int r = EMO_WAVE / per * m + lane / per, c = lane % per;
     const float v = stg[(c < n ? c : 0) * 65 + r];
     const long long row = wbase + r;
     if (row < B && c < n) S[)" + row_of + R"( + c] = stg_bad[r] ? EMO_NAN : v;
