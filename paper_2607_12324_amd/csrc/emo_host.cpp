@@ -278,13 +278,11 @@ struct emo_graph_s {
     bool cut_ok = false;
     int cut_state = 0;                       // 0 not tried, 1 compiled, -1 failed
     emo::JitModule jk;
-    // time-interval kernels specialised to the graph
-    // (workgroups of 256, 512 and 1024 candidates, each compiled on first use)
-    struct IvKernel {
-        int state = 0;                       // 0 not tried, 1 compiled, -1 failed
-        emo::JitModule m;
-        int64_t cap_key = -1, cap = 0;       // resident workgroups for the last (K, M)
-    } iv[3];
+    // time-interval kernel specialised to the graph, compiled on the first call and launched at
+    // workgroups of 256, 512 or 1024 candidates
+    int iv_state = 0;                        // 0 not tried, 1 compiled, -1 failed
+    emo::JitModule jiv;
+    int64_t iv_cap_key[3] = {-1, -1, -1}, iv_cap[3] = {};   // resident workgroups for the last (K, M) of each size
     Arena arena;                             // per-call scratch, kept between calls
     Arena dp_arena;                          // scratch of the policy search (whose evaluations
                                              // use `arena`)
@@ -633,7 +631,7 @@ void release_device(emo_graph_s *g) {
         emo::jit_unload(&g->jn);
         emo::jit_unload(&g->jc);
         emo::jit_unload(&g->jk);
-        for (emo_graph_s::IvKernel &k : g->iv) emo::jit_unload(&k.m);
+        emo::jit_unload(&g->jiv);
         for (void *p : g->allocations) (void)hipFree(p);
         arena_free(g->arena);
         arena_free(g->dp_arena);
@@ -913,31 +911,23 @@ emo::JitSlack jit_slack(const emo_graph_s &g) {
     return g.jit_slack_eligible ? emo::JitSlack::kPacks : emo::JitSlack::kNone;
 }
 
-size_t iv_table_bytes(const emo_graph_s &g) {
-    const size_t tb = static_cast<size_t>(g.P) * g.F * sizeof(float2);
-    return tb <= emo::kJitTableLds ? tb : 0;   // 0: read from device memory
-}
-
-// Generates and compiles the time-interval kernel of `block` candidates a workgroup once; *out is its
-// record, ready when the result is 1.
-int ensure_iv(emo_graph_s *g, int block, emo_graph_s::IvKernel **out) {
+// Generates and compiles the time-interval kernel once; returns 1 when it is ready.
+int ensure_iv(emo_graph_s *g) {
     std::lock_guard<std::mutex> lock(g->jit_mu);
-    emo_graph_s::IvKernel &k = g->iv[block == 256 ? 0 : block == 512 ? 1 : 2];
-    *out = &k;
-    if (k.state != 0) return k.state;
-    const bool tab_lds = static_cast<size_t>(g->P) * g->F * sizeof(float2) <= emo::kJitTableLds;
-    const std::string src = emo::jit_generate_intervals(g->jg, tab_lds, block);
+    if (g->iv_state != 0) return g->iv_state;
+    const int bound = emo::jit_iv_bound(g->jg, g->info.eval_slots);
+    const std::string src = emo::jit_generate_intervals(g->jg, bound);
     DeviceGuard guard(g->device);
     emo::JitModule m;
     std::string log;
     if (emo::jit_compile_intervals(src, &m, &log) != 0) {
         g->jit_log = log;
-        k.state = -1;
+        g->iv_state = -1;
         return -1;
     }
-    m.block = block;
-    k.m = m;
-    k.state = 1;
+    m.block = bound;
+    g->jiv = m;
+    g->iv_state = 1;
     g->info.compile_seconds += static_cast<float>(m.compile_seconds);
     return 1;
 }
@@ -1437,8 +1427,7 @@ emo_status emo_graph_cut_source(emo_graph_t g, char *buf, int64_t *len) {
 emo_status emo_graph_interval_source(emo_graph_t g, char *buf, int64_t *len) {
     if (!g || !len) return fail(EMO_ERR_INVALID_ARGUMENT, "NULL argument");
     if (!g->jit_eligible) return fail(EMO_ERR_UNSUPPORTED, "graph too large for one specialised kernel");
-    const size_t tb = static_cast<size_t>(g->P) * g->F * sizeof(float2);
-    const std::string src = emo::jit_generate_intervals(g->jg, tb <= emo::kJitTableLds, 256);
+    const std::string src = emo::jit_generate_intervals(g->jg, emo::jit_iv_bound(g->jg, g->info.eval_slots));
     const int64_t need = static_cast<int64_t>(src.size()) + 1;
     if (!buf) {
         *len = need;
@@ -1669,15 +1658,14 @@ emo_status emo_eval_intervals(emo_graph_t g, const uint8_t *levels, int64_t B, i
     emo::IvJitArgs iva;
     bool use_jit = g->kernel_mode != EMO_KERNELS_INTERPRETED && g->jit_eligible &&
                    iv_buckets(pol.pts, num_intervals, &iva.scale, &iva.M);
-    emo_graph_s::IvKernel *ivk = nullptr;
+    int block = 0;
     if (use_jit) {
-        const int block = emo::jit_iv_block(iv_table_bytes(*g), num_intervals, iva.M, B);
-        const int state = ensure_iv(g, block, &ivk);
+        const int state = ensure_iv(g);
         if (state != 1 && g->kernel_mode == EMO_KERNELS_SPECIALIZED)
             return fail(EMO_ERR_DEVICE, "time-interval kernel compilation failed: %s", g->jit_log.c_str());
         // the rows and the bucket table must fit the workgroup's LDS beside the static tables
-        use_jit = state == 1 && ivk->m.iv_static_lds + emo::jit_iv_dyn_lds(block, num_intervals, iva.M) <=
-                                    static_cast<size_t>(ivk->m.iv_max_lds);
+        if (state == 1) block = emo::jit_iv_block(g->jiv, num_intervals, iva.M, B);
+        use_jit = block > 0;
     }
     int64_t iv_cap = 0;
     if (use_jit) {
@@ -1686,14 +1674,15 @@ emo_status emo_eval_intervals(emo_graph_t g, const uint8_t *levels, int64_t B, i
         std::memcpy(iva.idle, pol.idle, sizeof(iva.idle));
         // persistent workgroups (each builds the bucket table once): as many as are resident
         const int64_t key = static_cast<int64_t>(num_intervals) << 32 | iva.M;
+        const int size = block == 256 ? 0 : block == 512 ? 1 : 2;
         std::lock_guard<std::mutex> lock(g->jit_mu);
-        if (ivk->cap_key != key) {
-            ivk->cap = emo::jit_iv_cap(ivk->m, num_intervals, iva.M);
-            ivk->cap_key = key;
+        if (g->iv_cap_key[size] != key) {
+            g->iv_cap[size] = emo::jit_iv_cap(g->jiv, block, num_intervals, iva.M);
+            g->iv_cap_key[size] = key;
         }
-        iv_cap = ivk->cap;
+        iv_cap = g->iv_cap[size];
     }
-    const int64_t nblocks = use_jit ? emo::jit_blocks(ivk->m, false, B) : emo::forward_blocks(B);
+    const int64_t nblocks = use_jit ? emo::jit_iv_blocks(block, B) : emo::forward_blocks(B);
     const bool direct = result && nblocks == 1;   // (as in evaluate)
     size_t part_bytes = result && !direct ? static_cast<size_t>(nblocks) * emo::kPartialBytes : 0;
     part_bytes = (part_bytes + 255) & ~static_cast<size_t>(255);
@@ -1714,7 +1703,7 @@ emo_status emo_eval_intervals(emo_graph_t g, const uint8_t *levels, int64_t B, i
     g->info.last_kernels = use_jit ? 7 : 0;
     hipError_t e = g->ev_begin ? hipEventRecord(g->ev_begin, st) : hipSuccess;
     if (e == hipSuccess && use_jit)
-        e = emo::jit_launch_intervals(ivk->m, levels, B, g->dg.tab, iva, iv_cap, makespan, energy, tg, st);
+        e = emo::jit_launch_intervals(g->jiv, block, levels, B, g->dg.tab, iva, iv_cap, makespan, energy, tg, st);
     else if (e == hipSuccess)
         e = emo::launch_intervals(g->dg, pol, levels, B, makespan, energy, tg, work, st);
     if (e == hipSuccess && g->ev_end) e = hipEventRecord(g->ev_end, st);

@@ -452,18 +452,22 @@ struct IvJitArgs {
     float pts[kMaxIntervals - 1];
     float idle[kMaxLevels];
 };
-std::string jit_generate_intervals(const JitGraph &g, bool tab_lds, int block);
+// The largest workgroup of the graph's kernel (256, 512 or 1024), with `live` finish times live at once; it
+// is launched at that size or less.
+int jit_iv_bound(const JitGraph &g, int live);
+std::string jit_generate_intervals(const JitGraph &g, int bound);
 int jit_compile_intervals(const std::string &src, JitModule *out, std::string *log);
-// Dynamic LDS bytes of emo_iv for K intervals and M buckets (bucket table, then the rows).
+// Dynamic LDS bytes of emo_iv for K intervals and M buckets (bucket table, rows, a flag per row).
 size_t jit_iv_dyn_lds(int block, int K, int M);
-// Candidates per workgroup (256, 512 or 1024) of emo_iv for a table of table_bytes in LDS: the
-// smallest that keeps nearly the most waves of a compute unit busy (one table copy a workgroup, so a
-// large table needs large workgroups; past 16 waves more do not help) and that B candidates fill the
-// device with.
-int jit_iv_block(size_t table_bytes, int K, int M, int64_t B);
+// Candidates per workgroup of a call: 256, 512 or 1024, at most the kernel's bound (m.block) and with
+// room in LDS; the smallest that keeps nearly the most waves of a compute unit busy (one table copy a
+// workgroup, so a large table needs large workgroups; past 16 waves more do not help) and that B
+// candidates fill the device with.  0 when not even 256 fit.
+int jit_iv_block(const JitModule &m, int K, int M, int64_t B);
+int64_t jit_iv_blocks(int block, int64_t B);   // candidate groups of a call
 // Resident workgroups of emo_iv on the current device with that dynamic LDS (0: unknown).
-int64_t jit_iv_cap(const JitModule &m, int K, int M);
-hipError_t jit_launch_intervals(const JitModule &m, const uint8_t *levels, int64_t B, const float2 *tab,
+int64_t jit_iv_cap(const JitModule &m, int block, int K, int M);
+hipError_t jit_launch_intervals(const JitModule &m, int block, const uint8_t *levels, int64_t B, const float2 *tab,
                                 const IvJitArgs &a, int64_t cap, float *T, float *E, const SelTargets &tg,
                                 hipStream_t s);
 // Sets select_cap / slack_cap from the occupancy of the compiled kernels (current device).

@@ -651,21 +651,34 @@ std::string jit_generate(const JitGraph &g, JitSlack slack) {
 //
 // A step is a chain of three LDS reads (bucket, level byte, table entry), so what bounds the kernel is
 // their latency: waves per compute unit.  A 64 KB table leaves room for two workgroups, whatever their
-// size, so these take 512 or 1,024 candidates (jit_iv_block).  The rows in LDS hold each level times the
-// table stride (up to 32 levels), invalid ones replaced when the rows are copied, so a byte read is
-// the table address and the step needs no clamp.  512 packs of 16 levels, 2^20 candidates: 16 intervals
+// size, so these take 512 or 1,024 candidates (jit_iv_block).  One kernel serves every size: it is compiled
+// for the largest (jit_iv_bound) and reads its size at run time, since a graph of 2,000 packs takes 50 s to
+// compile and a call with fewer candidates or other change points must not wait for that again.  The rows
+// in LDS hold each level times the table stride (up to 32 levels), invalid ones replaced when the rows
+// are copied, so a byte read is the table address and the step needs no clamp.  512 packs of 16 levels, 2^20 candidates: 16 intervals
 // 350 us with workgroups of 256 (8 waves a compute unit), 163 with 512 (16 waves); 64 intervals 741 and
 // 258 (one workgroup of 1,024).  The energy and finish times pass an asm every 4 steps: at 8 or 16 the
 // compiler takes more than 128 registers and half the waves (16 intervals: 297 and 316 us against 180).
 
 namespace {
+bool iv_tab_lds(const JitGraph &g) { return static_cast<size_t>(g.P) * g.F * sizeof(float2) <= kJitTableLds; }
 int iv_level_shift(const JitGraph &g) { return g.F <= 32 ? 3 : 0; }   // (31 * 8 fits a byte)
 unsigned iv_level_mask(const JitGraph &g) { return static_cast<unsigned>(g.F - 1) * 0x01010101u; }
 }  // namespace
 
-std::string jit_generate_intervals(const JitGraph &g, bool tab_lds, int block) {
+// 1,024 candidates leave a lane 128 registers, 512 256: that holds 49 finish times live at once in 121
+// registers and 124 in 171, while 69 spill 8 registers at 1,024.  A table in device memory has no copy to
+// share.
+int jit_iv_bound(const JitGraph &g, int live) {
+    if (!iv_tab_lds(g)) return 256;
+    return live <= 64 ? 1024 : live <= 128 ? 512 : 256;
+}
+
+std::string jit_generate_intervals(const JitGraph &g, int bound) {
+    const bool tab_lds = iv_tab_lds(g);
     std::ostringstream o;
-    o << "#define EMO_BLOCK " << block << "\n" << kPrelude << kEmoSelectSource << "\n";
+    o << "#define EMO_BLOCK " << bound << "\n" << (bound > 256 ? "#define EMO_GROUP ((int)blockDim.x)\n" : "") << kPrelude
+      << kEmoSelectSource << "\n";
     const long long ntab = static_cast<long long>(g.P) * g.F;
     o << "#define NTAB " << (ntab > 0 ? ntab : 1) << "\n";
     o << "#define EMO_F " << g.F << "\n";
@@ -772,35 +785,38 @@ struct EmoFwd { float T; float E; };
     // a table in device memory: registers for several table reads in flight rather than more waves (the
     // compiler otherwise orders the steps to save registers and waits for each read: 900 packs of 24
     // levels, 131,072 candidates, 176 us that way)
+    // at 1,024 candidates four waves a SIMD, with all their registers: left to itself the compiler saves
+    // registers for waves that the LDS has no room for (512 packs: 47 registers and 45 us, with 98 40 us)
     o << "extern \"C\" __global__ void __launch_bounds__(EMO_BLOCK)"
-      << (tab_lds ? "" : " __attribute__((amdgpu_waves_per_eu(1, 3)))") << "\n"
+      << (tab_lds ? (bound == 1024 ? " __attribute__((amdgpu_waves_per_eu(4, 4)))" : "") : " __attribute__((amdgpu_waves_per_eu(1, 3)))") << "\n"
          "emo_iv(const u8 *__restrict__ lv, long long B, const float2 *__restrict__ tabg, EmoIvArgs a,\n"
          "    int copy, float inv_k, float *__restrict__ To, float *__restrict__ Eo, EmoTargets tg) {\n";
     if (tab_lds)
         o << "  __shared__ float2 tab[NTAB];\n"
-             "  for (int i_ = threadIdx.x; i_ < NTAB; i_ += EMO_BLOCK) tab[i_] = tabg[i_];\n";
+             "  for (int i_ = threadIdx.x; i_ < NTAB; i_ += EMO_GROUP) tab[i_] = tabg[i_];\n";
     else
         o << "  const float2 *__restrict__ tab = tabg;\n";
     o << R"(  __shared__ float s_pts[256];
   __shared__ double s_dur[256];      // interval lengths T_{i+1} - T_i (T_0 = 0)
   __shared__ float s_idle[256];      // zero past F
-  __shared__ u8 s_bad[EMO_BLOCK];    // the row holds an invalid level
-  // dynamic: the bucket table (M entries), then the group's rows, SD words a row
+  // dynamic: the bucket table (M entries), then the group's rows, SD words a row, then a byte a row
+  // (it holds an invalid level)
   extern __shared__ __align__(16) unsigned int emo_dyn[];
   const int K = a.K, M = a.M;
   const int SD = ((K + 3) >> 2) | 1;        // odd: a word column of the rows is conflict free
   int2 *s_bk = (int2 *)emo_dyn;
   unsigned int *s_rows = emo_dyn + 2 * M;
+  u8 *s_bad = (u8 *)(s_rows + EMO_GROUP * SD);
   const float scale = a.scale;
   s_bad[threadIdx.x] = 0;
-  for (int i = threadIdx.x; i < K - 1; i += EMO_BLOCK) s_pts[i] = a.pts[i];
-  for (int i = threadIdx.x; i < K - 1; i += EMO_BLOCK)
+  for (int i = threadIdx.x; i < K - 1; i += EMO_GROUP) s_pts[i] = a.pts[i];
+  for (int i = threadIdx.x; i < K - 1; i += EMO_GROUP)
     s_dur[i] = (double)a.pts[i] - (i > 0 ? (double)a.pts[i - 1] : 0.0);
-  for (int i = threadIdx.x; i < 256; i += EMO_BLOCK) s_idle[i] = i < EMO_F ? a.idle[i] : 0.f;
+  for (int i = threadIdx.x; i < 256; i += EMO_GROUP) s_idle[i] = i < EMO_F ? a.idle[i] : 0.f;
   __syncthreads();
   // bucket b: the number of points whose bucket is below b (they are increasing, and so are
   // their buckets), and the point whose bucket is b, if any
-  for (int b = threadIdx.x; b < M; b += EMO_BLOCK) {
+  for (int b = threadIdx.x; b < M; b += EMO_GROUP) {
     int lo = 0, hi = K - 1;
     while (lo < hi) {
       const int mid = (lo + hi) >> 1;
@@ -809,17 +825,17 @@ struct EmoFwd { float T; float E; };
     const float c = lo < K - 1 && (int)(s_pts[lo] * scale) == b ? s_pts[lo] : __builtin_inff();
     s_bk[b] = make_int2(lo, __float_as_int(c));
   }
-  for (long long grp = blockIdx.x; grp * EMO_BLOCK < B; grp += gridDim.x) {
+  for (long long grp = blockIdx.x; grp * EMO_GROUP < B; grp += gridDim.x) {
     // the group's rows are contiguous: copy them to LDS with coalesced loads of `copy` bytes
     // (16 when K is a multiple of 16, 4 when of 4, else 1; the batch aligned to match).  Row of
     // byte x: floor((x + 0.5) / K), exact from the fp32 product for x < 2^22.
     __syncthreads();   // the previous group's rows are read (and the tables built)
     {
-      const long long r0 = grp * EMO_BLOCK;
-      const int nb = (int)(B - r0 < EMO_BLOCK ? B - r0 : EMO_BLOCK) * K;
+      const long long r0 = grp * EMO_GROUP;
+      const int nb = (int)(B - r0 < EMO_GROUP ? B - r0 : EMO_GROUP) * K;
       const u8 *src = lv + r0 * K;
       if (copy == 16) {
-        for (int q = threadIdx.x; q < (nb >> 4); q += EMO_BLOCK) {
+        for (int q = threadIdx.x; q < (nb >> 4); q += EMO_GROUP) {
           const emo_u32x4 w = ((const emo_u32x4 *)src)[q];
           const int r = (int)(((float)(q << 4) + 0.5f) * inv_k);
           unsigned int *d = s_rows + r * SD + (((q << 4) - r * K) >> 2);
@@ -831,7 +847,7 @@ struct EmoFwd { float T; float E; };
           if (bad) s_bad[r] = 1;
         }
       } else if (copy == 4) {
-        for (int q = threadIdx.x; q < (nb >> 2); q += EMO_BLOCK) {
+        for (int q = threadIdx.x; q < (nb >> 2); q += EMO_GROUP) {
           const unsigned int w = ((const unsigned int *)src)[q];
           const int r = (int)(((float)(q << 2) + 0.5f) * inv_k);
           unsigned int bad = 0u;
@@ -839,7 +855,7 @@ struct EmoFwd { float T; float E; };
           if (bad) s_bad[r] = 1;
         }
       } else {
-        for (int q = threadIdx.x; q < nb; q += EMO_BLOCK) {
+        for (int q = threadIdx.x; q < nb; q += EMO_GROUP) {
           const int r = (int)(((float)q + 0.5f) * inv_k);
           unsigned int bad = 0u;
           ((u8 *)s_rows)[((r * SD) << 2) + q - r * K] = (u8)emo_iv_word(src[q], &bad);
@@ -848,7 +864,7 @@ struct EmoFwd { float T; float E; };
       }
     }
     __syncthreads();
-    const long long gid = grp * EMO_BLOCK + threadIdx.x;
+    const long long gid = grp * EMO_GROUP + threadIdx.x;
     const bool active = gid < B;
     const long long cand = active ? gid : B - 1;
     // (a lane past the batch walks the group's first row)
@@ -1788,20 +1804,23 @@ int jit_compile_intervals(const std::string &src, JitModule *out, std::string *l
 
 size_t jit_iv_dyn_lds(int block, int K, int M) {
     const size_t sd = static_cast<size_t>(((K + 3) >> 2) | 1);
-    return static_cast<size_t>(M) * 8 + static_cast<size_t>(block) * sd * 4;
+    return static_cast<size_t>(M) * 8 + static_cast<size_t>(block) * (sd * 4 + 1);
 }
 
-int jit_iv_block(size_t table_bytes, int K, int M, int64_t B) {
+int jit_iv_block(const JitModule &m, int K, int M, int64_t B) {
     // waves of a compute unit whose workgroups of `block` candidates share one table copy each
-    auto waves = [&](int block) {
-        const size_t lds = table_bytes + 4096 + static_cast<size_t>(block) + 512 + jit_iv_dyn_lds(block, K, M);
+    auto waves = [&](int block) -> int64_t {
+        const size_t lds = static_cast<size_t>(m.iv_static_lds) + jit_iv_dyn_lds(block, K, M);
+        if (lds > static_cast<size_t>(m.iv_max_lds)) return 0;
         return std::min<int64_t>(16, static_cast<int64_t>(kLdsBytes / lds) * block / 64);
     };
     int best = 256;
-    for (int block : {512, 1024})
+    for (int block = 512; block <= m.block; block *= 2)
         if (B >= 256 * static_cast<int64_t>(block) && waves(block) * 8 > waves(best) * 9) best = block;
-    return best;
+    return waves(best) > 0 ? best : 0;
 }
+
+int64_t jit_iv_blocks(int block, int64_t B) { return grid_of(B, block); }
 
 int64_t jit_blocks(const JitModule &m, bool slack, int64_t B) { return grid_of(B, slack ? m.slack_block : m.block); }
 
@@ -1828,7 +1847,7 @@ void jit_set_caps(JitModule *m) {
     m->slack_cap = resident_blocks(m->slack, m->slack_block);
 }
 
-hipError_t jit_launch_intervals(const JitModule &m, const uint8_t *levels, int64_t B, const float2 *tab,
+hipError_t jit_launch_intervals(const JitModule &m, int block, const uint8_t *levels, int64_t B, const float2 *tab,
                                 const IvJitArgs &a, int64_t cap, float *T, float *E, const SelTargets &tg,
                                 hipStream_t s) {
     SelTargets dt = tg;
@@ -1838,17 +1857,17 @@ hipError_t jit_launch_intervals(const JitModule &m, const uint8_t *levels, int64
     int copy = a.K % 16 == 0 && al % 16 == 0 ? 16 : (a.K % 4 == 0 && al % 4 == 0 ? 4 : 1);
     float inv_k = static_cast<float>(1.0 / a.K);
     void *args[] = {&levels, &b, &tab, &args_v, &copy, &inv_k, &T, &E, &dt};
-    const unsigned dyn = static_cast<unsigned>(jit_iv_dyn_lds(m.block, a.K, a.M));
-    return hipModuleLaunchKernel(m.select, capped_grid(B, m.block, cap), 1, 1, m.block, 1, 1, dyn, s, args,
+    const unsigned dyn = static_cast<unsigned>(jit_iv_dyn_lds(block, a.K, a.M));
+    return hipModuleLaunchKernel(m.select, capped_grid(B, block, cap), 1, 1, block, 1, 1, dyn, s, args,
                                  nullptr);
 }
 
-int64_t jit_iv_cap(const JitModule &m, int K, int M) {
+int64_t jit_iv_cap(const JitModule &m, int block, int K, int M) {
     int dev = 0, ncu = 0, nb = 0;
-    const size_t dyn = jit_iv_dyn_lds(m.block, K, M);
+    const size_t dyn = jit_iv_dyn_lds(block, K, M);
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipModuleOccupancyMaxActiveBlocksPerMultiprocessor(&nb, m.select, m.block, dyn) != hipSuccess ||
+        hipModuleOccupancyMaxActiveBlocksPerMultiprocessor(&nb, m.select, block, dyn) != hipSuccess ||
         nb < 1) {
         (void)hipGetLastError();
         return 0;

@@ -240,3 +240,27 @@ def test_intervals_workgroups_and_level_bytes(torch, emo, graph, B, K):
     for a, b in zip(*got):
         nan = (a.view(np.float32) != a.view(np.float32)) & (b.view(np.float32) != b.view(np.float32))
         assert np.array_equal(a[~nan], b[~nan])
+
+
+def test_intervals_compile_once_for_every_size(torch, emo):
+    """One kernel serves workgroups of 256, 512 and 1,024 candidates: after a graph's first call, calls
+    with other batch sizes, interval counts and change points compile nothing, and give the interpreting
+    kernel's bits."""
+    g = synth.config_graph(3)
+    P, F = g.num_packs, g.num_levels
+    T0 = float(oracle.eval_batch(g, np.full((1, P), F - 1, np.uint8))[0][0])
+    idle = [1.0 + 0.25 * i for i in range(F)]
+    ga, gi = emo.EmoGraph(g, device=0), emo.EmoGraph(g, device=0, kernel_mode=emo.KERNELS_INTERPRETED)
+    rng = np.random.default_rng(9)
+    seconds = None
+    for B, K in ((1, 16), (131072, 16), (262144, 64), (700, 3), (131072, 7)):
+        pts = [float(synth.quantize(1.05 * T0 * (i + 1 + 0.3 * rng.random()) / K)) for i in range(K - 1)]
+        lv = dev(torch, rng.integers(0, F, (B, K)).astype(np.uint8))
+        print(f"[case] intervals compiled once B={B} K={K}", flush=True)
+        a, b = ga.eval_intervals(lv, pts, idle), gi.eval_intervals(lv, pts, idle)
+        assert ga.info()["last_kernels"] == 7
+        assert all(torch.equal(x.view(torch.int32), y.view(torch.int32)) for x, y in zip(a[:2], b[:2]))
+        seconds = ga.info()["compile_seconds"] if seconds is None else seconds
+        assert ga.info()["compile_seconds"] == seconds > 0
+    ga.close()
+    gi.close()

@@ -210,3 +210,17 @@ def test_interval_kernels_compile(emo, hiprtc, tmp_path, k):
     src = emo.EmoGraph(g, device=-1).interval_source()
     path = compile_source(hiprtc, src, tmp_path)
     notes, asm = check_code_object(path, ["emo_iv"])
+
+
+@pytest.mark.parametrize("kind, bound", [("training", 1024), ("chains-40", 1024), ("wide", 512), ("large-table", 256)])
+def test_interval_kernel_of_every_bound(emo, hiprtc, tmp_path, kind, bound):
+    """The time-interval kernel is compiled once, for the largest workgroup that its live finish times
+    leave enough registers for, and spills none there."""
+    g = {"training": lambda: synth.config_graph(3), "chains-40": lambda: synth.stream_graph(1, 400, 40, 4),
+         "wide": lambda: synth.random_dag(np.random.default_rng(1), 300, 0.03, 0.8, 8, shuffle_ids=False,
+                                          shuffle_packs=False),
+         "large-table": lambda: synth.packed_graph(5, 600, 4, 24, sync_every=700)}[kind]()
+    src = emo.EmoGraph(g, device=-1).interval_source()
+    assert int(re.search(r"#define EMO_BLOCK (\d+)", src).group(1)) == bound
+    notes, _ = check_code_object(compile_source(hiprtc, src, tmp_path), ["emo_iv"])
+    assert notes["emo_iv"][0] <= 512 * 256 // bound, notes
