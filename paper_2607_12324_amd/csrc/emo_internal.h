@@ -452,6 +452,7 @@ struct IvJitArgs {
     float pts[kMaxIntervals - 1];
     float idle[kMaxLevels];
 };
+bool jit_iv_table_in_lds(const JitGraph &g);   // else read from device memory
 // The largest workgroup of the graph's kernel (256, 512 or 1024), with `live` finish times live at once; it
 // is launched at that size or less.
 int jit_iv_bound(const JitGraph &g, int live);

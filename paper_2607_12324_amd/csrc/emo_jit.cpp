@@ -661,21 +661,22 @@ std::string jit_generate(const JitGraph &g, JitSlack slack) {
 // compiler takes more than 128 registers and half the waves (16 intervals: 297 and 316 us against 180).
 
 namespace {
-bool iv_tab_lds(const JitGraph &g) { return static_cast<size_t>(g.P) * g.F * sizeof(float2) <= kJitTableLds; }
 int iv_level_shift(const JitGraph &g) { return g.F <= 32 ? 3 : 0; }   // (31 * 8 fits a byte)
 unsigned iv_level_mask(const JitGraph &g) { return static_cast<unsigned>(g.F - 1) * 0x01010101u; }
 }  // namespace
+
+bool jit_iv_table_in_lds(const JitGraph &g) { return static_cast<size_t>(g.P) * g.F * sizeof(float2) <= kJitTableLds; }
 
 // 1,024 candidates leave a lane 128 registers, 512 256: that holds 49 finish times live at once in 121
 // registers and 124 in 171, while 69 spill 8 registers at 1,024.  A table in device memory has no copy to
 // share.
 int jit_iv_bound(const JitGraph &g, int live) {
-    if (!iv_tab_lds(g)) return 256;
+    if (!jit_iv_table_in_lds(g)) return 256;
     return live <= 64 ? 1024 : live <= 128 ? 512 : 256;
 }
 
 std::string jit_generate_intervals(const JitGraph &g, int bound) {
-    const bool tab_lds = iv_tab_lds(g);
+    const bool tab_lds = jit_iv_table_in_lds(g);
     std::ostringstream o;
     o << "#define EMO_BLOCK " << bound << "\n" << (bound > 256 ? "#define EMO_GROUP ((int)blockDim.x)\n" : "") << kPrelude
       << kEmoSelectSource << "\n";
@@ -782,13 +783,18 @@ struct EmoFwd { float T; float E; };
         o << "  const unsigned int m = " << bad_word << ";\n"
              "  *bad |= m;\n"
              "  return (w & ~(m | (m - (m >> 7)))) << " << shift << ";\n}\n";
-    // a table in device memory: registers for several table reads in flight rather than more waves (the
-    // compiler otherwise orders the steps to save registers and waits for each read: 900 packs of 24
-    // levels, 131,072 candidates, 176 us that way)
+    // A table in device memory: registers for several table reads in flight rather than the most waves
+    // (left to itself the compiler orders the steps to save registers and waits for each read: 900 packs of
+    // 24 levels, 100,000 candidates 167 us, at most four waves a SIMD 111, three 99).  Few packs need fewer
+    // registers for that, and a fifth wave serves batches that four leave a nearly empty last round: 300
+    // packs of 40 levels, 300,000 candidates 82 us with four, 56 with five, and with three 77 us already at
+    // 2^18 against 47.  At 500 packs of 24 levels five are still ahead of four there (86 and 118).
+    const char *const dev_waves = g.ops.size() <= 512 ? " __attribute__((amdgpu_waves_per_eu(1, 5)))"
+                                                      : " __attribute__((amdgpu_waves_per_eu(1, 4)))";
     // at 1,024 candidates four waves a SIMD, with all their registers: left to itself the compiler saves
     // registers for waves that the LDS has no room for (512 packs: 47 registers and 45 us, with 98 40 us)
     o << "extern \"C\" __global__ void __launch_bounds__(EMO_BLOCK)"
-      << (tab_lds ? (bound == 1024 ? " __attribute__((amdgpu_waves_per_eu(4, 4)))" : "") : " __attribute__((amdgpu_waves_per_eu(1, 3)))") << "\n"
+      << (tab_lds ? (bound == 1024 ? " __attribute__((amdgpu_waves_per_eu(4, 4)))" : "") : dev_waves) << "\n"
          "emo_iv(const u8 *__restrict__ lv, long long B, const float2 *__restrict__ tabg, EmoIvArgs a,\n"
          "    int copy, float inv_k, float *__restrict__ To, float *__restrict__ Eo, EmoTargets tg) {\n";
     if (tab_lds)

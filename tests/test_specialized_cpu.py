@@ -224,3 +224,12 @@ def test_interval_kernel_of_every_bound(emo, hiprtc, tmp_path, kind, bound):
     assert int(re.search(r"#define EMO_BLOCK (\d+)", src).group(1)) == bound
     notes, _ = check_code_object(compile_source(hiprtc, src, tmp_path), ["emo_iv"])
     assert notes["emo_iv"][0] <= 512 * 256 // bound, notes
+
+
+@pytest.mark.parametrize("P,F,waves", [(300, 40, 5), (400, 24, 5), (600, 24, 4)])
+def test_interval_kernel_with_device_table_keeps_its_waves(emo, hiprtc, tmp_path, P, F, waves):
+    """A table past LDS: registers for five waves a SIMD up to 512 packs, for four above (fewer waves leave
+    a batch a nearly empty last round)."""
+    src = emo.EmoGraph(synth.packed_graph(P, P, 4, F, sync_every=P + 1, cross_p=0.05), device=-1).interval_source()
+    notes, _ = check_code_object(compile_source(hiprtc, src, tmp_path), ["emo_iv"])
+    assert notes["emo_iv"][0] <= 512 // waves // 8 * 8, notes
