@@ -391,8 +391,10 @@ emo_status emo_graph_set_timing_events(emo_graph_t g, void *begin_event, void *e
  * candidates each.  When the packs are set in the order the evaluators visit them (pack_order NULL or
  * the identity, and pack_order_monotone 1), exact_time_sums is 1 and the buckets fit one workgroup
  * (buckets x F at most 16,384, and the stored policies' live finish times in its LDS), one kernel runs
- * all stages with the same results bit for bit and 4 bytes x buckets x P of scratch; interpreted mode
- * always searches by stages.  Not to be called concurrently with itself on the same graph.
+ * all stages with the same results bit for bit and 4 bytes x buckets x P of scratch, unless many fixed
+ * nodes follow the packs (each takes that kernel longer than the launches it saves: more than about 100
+ * per pack on one stream, 5 on 40).  Every other search goes by stages: among them those of graphs with
+ * times off the exact grid, as measured durations are, and all in interpreted mode.  Not to be called concurrently with itself on the same graph.
  */
 emo_status emo_dp_search(emo_graph_t g, float latency_target, float quantum, const int32_t *pack_order,
                          int32_t max_states, uint8_t *best_levels, emo_selection *result, void *stream);

@@ -1855,7 +1855,8 @@ bool search_in_one_kernel(emo_graph_s *g, const std::vector<int32_t> &order, int
                 sp.P = g->P;
                 sp.F = g->F;
                 sp.L = h.L;
-                sp.rec_words = h.rec_words;
+                sp.fixed = h.fixed;
+                sp.fixed_stages = h.fixed_stages;
                 sp.t_const = g->t_const;
                 sp.static_power = g->static_power;
                 if (upload(*g, h.recs, &sp.recs) == EMO_OK && upload(*g, h.fix, &sp.fix) == EMO_OK &&
@@ -1871,7 +1872,7 @@ bool search_in_one_kernel(emo_graph_s *g, const std::vector<int32_t> &order, int
     }
     if (g->search_state[v] != 1) return false;
     *prog = &g->search[v];
-    return emo::search_fits(g->F, g->search[v].L, NB);
+    return emo::search_fits(g->search[v], NB);
 }
 
 size_t dp_layout(int64_t S, int64_t R, int32_t P, DPBuffers *b, char *base) {

@@ -277,13 +277,15 @@ constexpr int kSearchMaxLive = 64;     // finish times kept per stored policy at
 struct SearchHost {
     int L = -1;                        // live finish times per policy (4, 8, 16, 32 or 64), or -1
     int rec_words = 0;
+    int fixed = 0, fixed_stages = 0;
     std::vector<uint32_t> recs, fix;
     std::vector<float> etop;
 };
 struct SearchProg {
-    int32_t P = 0, F = 1, L = 0, rec_words = 0;
+    int32_t P = 0, F = 1, L = 0;
+    int32_t fixed = 0, fixed_stages = 0;   // fixed nodes that follow a pack, and packs that some follow
     float t_const = 0.f, static_power = 0.f;
-    const uint32_t *recs = nullptr;    // [P][rec_words]
+    const uint32_t *recs = nullptr;    // [P][words of a record]
     const uint32_t *fix = nullptr;
     const float *etop = nullptr;       // [energy blocks + 2][kEnergyBlock], zero past a block's end
 };
@@ -294,8 +296,9 @@ struct SearchProg {
 SearchHost search_build(const JitGraph &g, const std::vector<float> &ttop, const std::vector<float> &etop,
                         const std::vector<float> &emin, const std::vector<float> &emax,
                         const std::vector<int32_t> &blk_end);
-// Whether NB buckets fit the kernel (its LDS, its record prefetch) and suit one workgroup.
-bool search_fits(int F, int L, int64_t NB);
+// Whether NB >= 1 buckets of a P >= 1 pack search fit the kernel (its LDS, its record prefetch) and a stage
+// of it takes less than the launches of a search by stages.
+bool search_fits(const SearchProg &g, int64_t NB);
 // The search over NB >= 1 buckets and P >= 1 packs.  scratch: P * NB back pointers (uint32).
 hipError_t launch_search(const SearchProg &g, const float2 *tab, float tmax, double q, int64_t bmin, int64_t NB,
                          void *scratch, uint8_t *best, emo_selection *res, hipStream_t s);

@@ -476,7 +476,9 @@ SearchHost search_build(const JitGraph &g, const std::vector<float> &ttop, const
             fx[kFixSink] = op.out.empty() ? 1u : 0u;
             for (int32_t k : op.in) fx[kFixHdr + slot[k]] = 0u;
             h.fix.insert(h.fix.end(), fx.begin(), fx.end());
-            h.recs[h.recs.size() - h.rec_words + kRecFixCount]++;   // (a pack precedes every such node)
+            // (a pack precedes every such node)
+            ++h.fixed;
+            if (h.recs[h.recs.size() - h.rec_words + kRecFixCount]++ == 0) ++h.fixed_stages;
             visit(i);
             continue;
         }
@@ -519,9 +521,20 @@ SearchHost search_build(const JitGraph &g, const std::vector<float> &ttop, const
 // (12,336 on 96 packs 0.99 against 1.90), and past this the lead shrinks.
 constexpr int64_t kSearchMaxCandidates = 16384;
 
-bool search_fits(int F, int L, int64_t NB) {
-    return kRecHdr + 2 * (F + L) + 3 <= kThreads && NB * F <= kSearchMaxCandidates &&
-           search_lds(F, L, static_cast<int>(NB)).total <= kSearchLds;
+bool search_fits(const SearchProg &g, int64_t NB) {
+    if (kRecHdr + 2 * (g.F + g.L) + 3 > kThreads || NB * g.F > kSearchMaxCandidates ||
+        search_lds(g.F, g.L, static_cast<int>(NB)).total > kSearchLds)
+        return false;
+    // us a stage here: candidates, the winner's live values, and the fixed nodes after a pack, which one
+    // thread per bucket walks one after another with L dependent reads each; fitted to measured stages
+    // (L 4: 2.1 with 1,024 candidates and 11.0 with 15,488; L 64: 3.8 with 256, 10.5 with 12,800; a pack's
+    // first fixed node 1.9 at L 32 and 2.1 to 3.1 at L 64, further ones as below).  A stage of a search by stages takes its launches at least: 12.4 us, 13.2 to 14.3 with 15,488 candidates
+    // (graphs of 12 to 40 packs).  Without this rule 40 packs on 40 chains with 12 fixed nodes a pack took
+    // 0.67 ms against 0.48 by stages, with 50 2.2 against 0.50.
+    const double cand = static_cast<double>(NB * g.F);
+    const double each = g.L == 4 ? 0.10 : g.L == 8 ? 0.14 : g.L == 16 ? 0.43 : g.L == 32 ? 0.69 : 1.2;
+    const double here = 1.5 + 0.0006 * cand + g.L / 30.0 + (each * g.fixed + 0.035 * g.L * g.fixed_stages) / g.P;
+    return here <= 12.0 + 0.0001 * cand;
 }
 
 namespace {

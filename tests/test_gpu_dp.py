@@ -212,3 +212,43 @@ def test_dp_one_kernel_matches_stages(torch, emo, kind):
     off = emo.EmoGraph(synth.scaled_times(g, 1.1), device=0)
     off.dp_search(float(np.float32(1.2 * T0)), T0)
     assert off.info()["last_kernels"] != 9
+
+
+def _chains_with_fixed(S, P, n, F, seed):
+    """P packs round-robin on S chains, n fixed nodes after each, and a last node that waits for all."""
+    rng = np.random.default_rng(seed)
+    src, dst, pack, dur, last = [], [], [], [], [-1] * S
+    for p in range(P):
+        for k in range(n + 1):
+            pack.append(p if k == 0 else -1)
+            dur.append(0.0 if k == 0 else float(rng.integers(1, 9)) / 4)
+            v = len(pack) - 1
+            if last[p % S] >= 0:
+                src.append(last[p % S])
+                dst.append(v)
+            last[p % S] = v
+    pack.append(-1)
+    dur.append(1.0)
+    src += last
+    dst += [len(pack) - 1] * S
+    t = np.sort(synth.quantize(rng.uniform(1, 9, (P, F))), axis=1)[:, ::-1].astype(np.float32).copy()
+    return synth.Graph("chains-fixed", len(pack), np.asarray(src, np.int32), np.asarray(dst, np.int32),
+                       np.asarray(pack, np.int32), np.asarray(dur, np.float32), P, F, t, (0.37 * t).astype(np.float32), 0.25)
+
+
+@pytest.mark.parametrize("S, P, n, one", [(1, 12, 50, True), (1, 12, 150, False), (12, 24, 9, True), (12, 24, 40, False),
+                                          (24, 24, 4, True), (24, 24, 18, False), (40, 40, 3, True), (40, 40, 12, False)])
+def test_dp_with_many_fixed_nodes(torch, emo, S, P, n, one):
+    """Fixed nodes after each pack cost the one-kernel search a chain of reads: past about the time of the
+    launches they save, the search goes by stages; the results are interpreted mode's on both sides."""
+    g = _chains_with_fixed(S, P, n, 8, 100 * S + n)
+    ga, gi = emo.EmoGraph(g, device=0), emo.EmoGraph(g, device=0, kernel_mode=emo.KERNELS_INTERPRETED)
+    T0 = float(dp.eval_batch(g, np.full((1, P), 7, np.uint8))[0][0])
+    tgt, q = float(np.float32(1.2 * T0)), float(np.float32(0.2 * T0 / 30))
+    print(f"[case] dp fixed nodes S={S} P={P} n={n} target={tgt}", flush=True)
+    a, sa = run(emo, ga, tgt, q)
+    assert (ga.info()["last_kernels"] == 9) == one
+    b, sb = run(emo, gi, tgt, q)
+    assert sa.index >= 0 and np.array_equal(a, b) and sa == sb
+    ga.close()
+    gi.close()
