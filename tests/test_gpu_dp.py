@@ -252,3 +252,97 @@ def test_dp_with_many_fixed_nodes(torch, emo, S, P, n, one):
     assert sa.index >= 0 and np.array_equal(a, b) and sa == sb
     ga.close()
     gi.close()
+
+
+def test_dp_energy_on_ragged_cut_segments(torch, emo):
+    """Cut-segment evaluators start their fp32 energy blocks anew at each segment: on segments of 160
+    packs (blocks of 64, 64 and 32) with non-dyadic energies, whose sums round differently under any
+    other split, the one-kernel search reports the found policy's evaluated energy and makespan."""
+    g = synth.packed_graph(8, 960, 5, 16, sync_every=160)
+    P, F = g.num_packs, g.num_levels
+    gh = emo.EmoGraph(g, device=0)
+    T0 = float(dp.eval_batch(g, np.full((1, P), F - 1, np.uint8))[0][0])
+    plain = 0
+    cases = [(r, nb) for r in (1.01, 1.02, 1.05, 1.1, 1.2, 1.3) for nb in (9, 64)]
+    for ratio, nb in cases:
+        tgt, q = float(np.float32(ratio * T0)), float(np.float32((ratio - 1.0) * T0 / nb))
+        print(f"[case] dp ragged cut segments target={tgt} buckets~{nb}", flush=True)
+        lv, res = gh.dp_search(tgt, q)
+        assert gh.info()["last_kernels"] == 9
+        sel = emo.parse_selection(res)
+        T, E = gh.eval_policies(lv[None, :].contiguous())
+        assert gh.info()["last_kernels"] == 5
+        assert sel.index >= 0 and float(T[0]) == sel.makespan and float(E[0]) == sel.energy, (sel, T, E)
+        # the same packs in blocks of 64 from the first one on: another fp32 sum
+        e = g.pack_energy[np.arange(P), lv.cpu().numpy()]
+        total = 0.0
+        for k in range(0, P, 64):
+            b = np.float32(0)
+            for x in e[k:k + 64]:
+                b = np.float32(b + x)
+            total += float(b)
+        plain += float(np.float32(total + g.static_power * sel.makespan)) == sel.energy
+    assert plain < len(cases) - 3   # (the test can tell the splits apart)
+    gh.close()
+
+
+@pytest.mark.parametrize("kind", ["least-energy-zero", "wide-range", "zero-block"])
+def test_dp_energies_that_could_round(torch, emo, kind):
+    """The one-kernel search needs every fp64 sum of block sums to be exact: a block that may sum to
+    zero, or block sums further apart than fp64 holds, take the search by stages, a block that is always
+    zero does not; the results are those of interpreted mode either way."""
+    g = synth.packed_graph(5, 131, 3, 11, sync_every=50)
+    e = g.pack_energy.copy()
+    if kind == "least-energy-zero":
+        e[64:128, 0] = 0.0
+    elif kind == "wide-range":
+        e[:64] *= np.float32(2.0 ** -60)
+    else:
+        e[:64] = 0.0
+    g = dataclasses.replace(g, pack_energy=e)
+    P, F = g.num_packs, g.num_levels
+    ga, gi = emo.EmoGraph(g, device=0), emo.EmoGraph(g, device=0, kernel_mode=emo.KERNELS_INTERPRETED)
+    T0 = float(dp.eval_batch(g, np.full((1, P), F - 1, np.uint8))[0][0])
+    tgt, q = float(np.float32(1.1 * T0)), float(np.float32(0.1 * T0 / 50))
+    print(f"[case] dp energies {kind} target={tgt}", flush=True)
+    a, sa = run(emo, ga, tgt, q)
+    assert (ga.info()["last_kernels"] == 9) == (kind == "zero-block")
+    b, sb = run(emo, gi, tgt, q)
+    assert sa.index >= 0 and np.array_equal(a, b) and sa == sb
+    ga.close()
+    gi.close()
+
+
+def test_dp_first_identity_search_under_capture(torch, emo):
+    """A search captured into a graph after only searches in another order warmed its stream: the one-kernel
+    search's program is not built during the capture (that allocates and copies), the captured search goes
+    by stages, and the next search outside builds it; every replay gives the eager result."""
+    g = synth.packed_graph(5, 131, 3, 11, sync_every=50)
+    P, F = g.num_packs, g.num_levels
+    T0 = float(dp.eval_batch(g, np.full((1, P), F - 1, np.uint8))[0][0])
+    tgt, q = float(np.float32(1.1 * T0)), float(np.float32(0.1 * T0 / 50))
+    gh = emo.EmoGraph(g, device=0)
+    lv = torch.zeros(P, dtype=torch.uint8, device="cuda")
+    res = torch.zeros(3, dtype=torch.int64, device="cuda")
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    print("[case] dp capture after a search in another order", flush=True)
+    with torch.cuda.stream(s):
+        gh.dp_search(tgt, q, np.arange(P)[::-1].copy(), best_levels=lv, result=res)
+    s.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s):
+        gh.dp_search(tgt, q, best_levels=lv, result=res)
+    assert gh.info()["last_kernels"] != 9
+    eager, sel = run(emo, gh, tgt, q)
+    assert gh.info()["last_kernels"] == 9 and sel.index >= 0
+    for _ in range(3):
+        lv.zero_()
+        res.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(lv.cpu().numpy(), eager) and emo.parse_selection(res) == sel
+        run(emo, gh, tgt, 2 * q)   # the program's own eager work between replays
+    del graph
+    gh.close()
