@@ -1816,8 +1816,11 @@ struct DPBuffers {
 //   - exact time sums (precomputed path tails then give the recurrence's makespan);
 //   - evaluating kernels that sum energies in program order: every kind but the chain kernels, with
 //     blocks of 64 packs (counted from each segment's start in the cut-segment kernels).
-// Interpreted mode keeps the search by stages.  With g->dp_arena.mu held.
-bool search_in_one_kernel(emo_graph_s *g, const std::vector<int32_t> &order, int64_t NB, const emo::SearchProg **prog) {
+// Interpreted mode keeps the search by stages, and so does a search that is being captured into a graph
+// before any has built the program (building allocates and copies, which would end the capture).  With
+// g->dp_arena.mu held.
+bool search_in_one_kernel(emo_graph_s *g, const std::vector<int32_t> &order, int64_t NB, hipStream_t st,
+                          const emo::SearchProg **prog) {
     if (g->kernel_mode == EMO_KERNELS_INTERPRETED || NB < 1 || g->P < 1) return false;
     if (!g->info.exact_time_sums || !g->jg.pack_monotone) return false;
     for (int32_t i = 0; i < g->P; ++i)
@@ -1831,6 +1834,11 @@ bool search_in_one_kernel(emo_graph_s *g, const std::vector<int32_t> &order, int
     }
     const int v = cut ? 1 : 0;
     if (g->search_state[v] == 0) {
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
+            (void)hipGetLastError();
+            return false;
+        }
         g->search_state[v] = -1;
         try {
             std::vector<int32_t> ends;
@@ -1940,7 +1948,7 @@ emo_status emo_dp_search(emo_graph_t g, float latency_target, float quantum, con
     DPBuffers b{};
     std::lock_guard<std::mutex> lock(g->dp_arena.mu);
     const emo::SearchProg *prog = nullptr;
-    const bool one = search_in_one_kernel(g, order, NB, &prog);
+    const bool one = search_in_one_kernel(g, order, NB, st, &prog);
     const size_t bytes = one ? static_cast<size_t>(P) * static_cast<size_t>(NB) * sizeof(uint32_t)
                              : dp_layout(S, R, P, &b, nullptr);
     void *base = nullptr;
