@@ -129,8 +129,11 @@ typedef struct {
                                      path leads from u to v (they never decide a maximum or a
                                      minimum; results are unchanged) */
     int32_t chain_window;         /* packs per window of the windowed chain-lane kernel, 0 when
-                                     it does not apply (more than 16 chains, a chain that goes
-                                     back to an earlier window, fewer than 16 packs); calls
+                                     it does not apply (more than 16 chains, more than 128
+                                     levels, a chain that goes back to an earlier window, fewer
+                                     than 16 packs or 2^21 and more, step blocks of 2 GiB in
+                                     all, slack rows of a workgroup past 4 GiB: one or two
+                                     chains of 128 levels and 2,093,000 packs); calls
                                      without slack use it on graphs that neither one kernel nor
                                      the segmented kernels take, when levels and slack are
                                      16-byte aligned */

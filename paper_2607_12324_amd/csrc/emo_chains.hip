@@ -465,8 +465,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t win_rsrc(const void *base, uin
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), static_cast<short>(0),
                                              static_cast<int>(bytes), 0x00020000);
 }
-// An offset past every planned buffer (they all hold less than 2^31 bytes, and a uniform offset
-// stays below 2^31 too): loads there read zeros and stores are dropped.
+// An offset past the tables and the step blocks (they hold less than 2^31 bytes, and a uniform offset
+// stays below 2^31 too): loads there read zeros.
 constexpr uint32_t kWinNoStore = 0x80000000u;
 
 // The copy of a window, with each thread's pieces at offsets fixed for the whole kernel: win_plan
@@ -653,6 +653,12 @@ __device__ __forceinline__ void win_mark_bad(const WinArgs &a, uint32_t badbits,
 // fixed for the whole kernel: a wave covers 4 candidates x 16 pieces when rows are long enough
 // (conflict-free LDS reads with the odd row pitch), else whole rows.  Global offsets are bytes from
 // the workgroup's first row at the window's first column (32-bit); slack rows are 4-byte aligned.
+// Slack rows of a workgroup may span up to 4 GiB (128 levels on one or two chains take workgroups of
+// 512 candidates: 4 GiB at 2^21 packs), so a store to drop goes past them: at win_no_slack, from which
+// the byte offset of any window (below 4 P) leads neither into the rows nor past 2^32.
+__host__ __device__ inline uint32_t win_no_slack(int32_t P) {
+    return 0xffffffe0u - 4u * static_cast<uint32_t>(P);
+}
 template <int NF>
 struct FlushPlan {
     uint32_t src[NF];   // LDS byte offset of the piece's first float
@@ -685,7 +691,7 @@ __device__ __forceinline__ FlushPlan<NF> flush_plan(const WinArgs &a, int64_t ro
         const bool ok = q < n && r < rows_left;
         f.src[j] = ok ? a.L.off_tile + 4u * static_cast<uint32_t>(r * (W + 1) + 4 * kk) : a.L.off_tile;
         f.dst[j] = ok ? 4u * (static_cast<uint32_t>(r) * static_cast<uint32_t>(P) + 4u * static_cast<uint32_t>(kk))
-                      : kWinNoStore;
+                      : win_no_slack(P);
         const float tr = tfin[ok ? r : 0];
         f.nan |= ok && tr != tr ? 1u << j : 0u;
     }
@@ -693,7 +699,7 @@ __device__ __forceinline__ FlushPlan<NF> flush_plan(const WinArgs &a, int64_t ro
 }
 
 // `rows`: the workgroup's slack rows (S from its first row, a range check at the batch's end);
-// pieces a thread does not have and rows past the batch store at kWinNoStore, which the range
+// pieces a thread does not have and rows past the batch store at win_no_slack, which the range
 // check drops, so no store needs a lane mask
 template <int NF>
 __device__ __forceinline__ void flush_window(const FlushPlan<NF> &f, __amdgpu_buffer_rsrc_t rows, const char *lds,
@@ -725,7 +731,7 @@ __device__ __forceinline__ void flush_last(const WinArgs &a, __amdgpu_buffer_rsr
         const uint32_t dst = r < rows_left && cc < cols
                                  ? 4u * (static_cast<uint32_t>(r) * static_cast<uint32_t>(P) +
                                          static_cast<uint32_t>((w << a.wlog) + cc))
-                                 : kWinNoStore;
+                                 : win_no_slack(P);
         __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rows, dst, 0, 0);
     }
 }
@@ -1094,11 +1100,11 @@ bool chain_window_fits(int32_t nc, int32_t F, int32_t W, int32_t blk_bytes, int3
     // a barrier and the shortest last round: 2,043 kernels on 6 streams, 100,003 candidates 452 us with one
     // group, 499 with two; 3,001 on 2 streams 650, 684, and 775 with eight; but each copies the window's
     // table, so past 16 levels (a table row larger than two groups' level bytes) two share it: 5,000
-    // kernels on 3 streams with 24 levels 796 and 730.  A workgroup's slack rows span less than 2^31
-    // bytes, and the copy has to fit the threads.
+    // kernels on 3 streams with 24 levels 796 and 730.  The copy has to fit the threads, and a
+    // workgroup's slack rows have 32-bit byte offsets.
     int G = F <= 16 || top == 1 ? 1 : 2;
     while (G <= top && !slots_compiled(win_slots(W, 64 * G, F, blk_bytes, 64 * G * nc))) ++G;
-    if (G > top || static_cast<int64_t>(64 * G) * P * 4 >= int64_t{1} << 31) return false;
+    if (G > top || static_cast<int64_t>(64 * G) * P * 4 > static_cast<int64_t>(win_no_slack(P))) return false;
     *groups = G;
     return true;
 }

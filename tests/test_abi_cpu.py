@@ -176,8 +176,7 @@ def test_chain_windows(emo):
     """Window width of the windowed chain kernel: the widest of 256, 128, ..., 16 packs whose
     LDS working set fits (two level windows of 16 // chains groups of 64 candidates, two table
     windows, two step blocks, the slack tile) and whose copy takes at most 4 pieces of 16 bytes
-    per thread (one piece for pack counts that are not multiples of 16, whose rows the kernel
-    copies from the dwords around each piece); none with more than 16 chains, more than 128
+    per thread (one level piece for pack counts that are not multiples of 16); none with more than 16 chains, more than 128
     levels or a chain that goes back to an earlier window."""
     expect = {1: 0, 2: 16, 3: 0, 4: 0, 5: 256}
     for k, win in expect.items():
@@ -198,6 +197,16 @@ def test_chain_windows(emo):
                         np.asarray(order, np.int32), np.zeros(48, np.float32), 48, 2, t, 0.5 * t, 0.1)
         inf = _load(emo, g).info()
         assert inf["chain_lanes"] == 1 and inf["chain_window"] == win, order[:20]
+
+
+@pytest.mark.parametrize("P, S, win", [((1 << 20) + 21, 1, 16), ((1 << 20) + 16, 2, 32), ((1 << 21) - 8192, 1, 16)])
+def test_chain_windows_of_large_graphs(emo, P, S, win):
+    """128 levels on one or two chains take workgroups of 512 candidates, whose slack rows pass 2 GiB from
+    2^20 packs on: the window is that of smaller graphs."""
+    src = np.arange(P - S, dtype=np.int32)
+    t = np.ones((P, 128), np.float32)
+    g = synth.Graph("long-chains", P, src, src + S, np.arange(P, dtype=np.int32), np.zeros(P, np.float32), P, 128, t, t, 0.25)
+    assert _load(emo, g).info()["chain_window"] == win
 
 
 def _cut_nodes(V, src, dst):

@@ -1219,3 +1219,45 @@ def test_one_kernel_slack_large_tables(torch, emo, P, F):
                 assert np.array_equal(a[~nan], b[~nan])
     ga.close()
     gi.close()
+
+
+def test_chain_scan_rows_past_two_gigabytes(torch, emo):
+    """One chain of 2^20 kernels with 128 levels: a workgroup's 512 slack rows span more than 2^31 bytes.
+    Makespans and slack (exact: whole times, every sum below 2^24) against the recurrence in fp64, in
+    rows on both sides of 2^31 bytes and in the ragged last workgroup."""
+    P, F, B, H = (1 << 20) + 21, 128, 515, 64
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    tab = torch.randint(1, 16, (P, F), generator=gen, device="cuda", dtype=torch.uint8)
+    times = tab.to(torch.float32).cpu().numpy()
+    # H nodes launched by the host hold back every (P / H)-th kernel until a time that binds in some rows
+    at = np.arange(1, H + 1) * (P // (H + 1))
+    hold = np.round(8.0 * at + np.linspace(-9000, 9000, H)).astype(np.float32)
+    src = np.concatenate([np.arange(P - 1), P + np.arange(H)]).astype(np.int32)
+    dst = np.concatenate([np.arange(1, P), at]).astype(np.int32)
+    pack = np.concatenate([np.arange(P), np.full(H, -1)]).astype(np.int32)
+    dur = np.concatenate([np.zeros(P, np.float32), hold])
+    g = synth.Graph("one-long-chain", P + H, src, dst, pack, dur, P, F, times, times * np.float32(0.5), 0.25)
+    gh = emo.EmoGraph(g, device=0)
+    assert gh.info()["exact_time_sums"] == 1 and gh.info()["chain_scan_window"] == 16
+    lv = torch.randint(0, F, (B, P), generator=gen, device="cuda", dtype=torch.uint8)
+    lv[300, P // 2] = F
+    print(f"[case] chain scan, rows past 2 GiB P={P} B={B}", flush=True)
+    T = torch.empty(B, dtype=torch.float32, device="cuda")
+    S = torch.full((B, P), -1.0, dtype=torch.float32, device="cuda")
+    gh.slack(lv, out=S, makespan=T)
+    assert gh.info()["last_kernels"] == 6
+    T2, _ = gh.eval_policies(lv)
+    assert torch.equal(T.view(torch.int32), T2.view(torch.int32))
+    floor = torch.zeros(P, dtype=torch.float64, device="cuda")
+    floor[torch.from_numpy(at).cuda()] = torch.from_numpy(hold.astype(np.float64)).cuda()
+    moved = 0
+    for r in (0, 1, 255, 256, 510, 511, 512, 514):
+        d = tab.gather(1, lv[r].long()[:, None])[:, 0].double()
+        pre = d.cumsum(0)
+        late = torch.cummax((floor - (pre - d)).clamp_min(0.0), 0).values
+        assert float(T[r]) == float(pre[-1] + late[-1]), r
+        assert torch.equal(S[r].double(), late[-1] - late), r
+        moved += int((late[-1] != late[0]).item())
+    assert moved > 0 and bool(torch.isnan(S[300]).all()) and bool(torch.isnan(T[300]))
+    gh.close()
