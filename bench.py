@@ -718,7 +718,7 @@ def run_workload(k, args, emo, synth, np, torch, graph=None, cpu_budget_s=20.0):
 
 def kernel_name(kind: int, slack: bool) -> str:
     """The evaluating kernel (or chain of kernels timed as one unit) of a kernel kind."""
-    return {2: "emo_chain", 3: "chains_kernel", 4: "chains_windowed", 5: "emo_cut", 6: "chains_scan", 8: "chains_scan_full",
+    return {2: "emo_chain", 3: "chains_kernel", 4: "chains_windowed", 5: "emo_cut", 6: "chains_windowed", 8: "chains_windowed",
             1: "emo_sp_slack" if slack else "emo_sp_select"}.get(
                 kind, "slack_kernel" if slack else "forward_kernel")
 

@@ -446,7 +446,6 @@ struct WinArgs {
 // (second pass), the step block.
 struct WinSlots {
     int lvl, tab8, tab4, blk;
-    __host__ __device__ int total() const { return lvl + tab8 + blk; }
 };
 __host__ __device__ inline WinSlots win_slots(int W, int NC, int F, int blk_bytes, int nt) {
     WinSlots s;
@@ -1094,7 +1093,10 @@ bool chain_window_fits(int32_t nc, int32_t F, int32_t W, int32_t blk_bytes, int3
     const WinLayout L = win_layout(W, 64 * top, F, top * nc, blk_bytes);
     const WinSlots sl = win_slots(W, 64 * top, F, blk_bytes, 64 * top * nc);
     if (L.total > kWinLds || !slots_compiled(sl)) return false;
-    // rows that are not 16-byte aligned: one level piece per thread
+    // Rows that are not 16-byte aligned take one level piece per thread, so windows half as wide on some
+    // chain counts.  Two pieces and the wider window measured both ways: 2,043 kernels on 6 streams 468 us
+    // against 447 with one, 9,001 on 3 787 against 810 (273 against 263 without slack), but 8,301 on 7 498
+    // against 571; no count of chains or packs separates these, so the narrower window stays.
     if (P % 16 != 0 && sl.lvl > 1) return false;
     // Groups of 64 candidates per workgroup.  Workgroups of one group leave the fewest waves waiting at
     // a barrier and the shortest last round: 2,043 kernels on 6 streams, 100,003 candidates 452 us with one
@@ -1178,7 +1180,10 @@ hipError_t launch_windowed_slots(const WinSlots &sl, const WinLaunch &l, const D
 // kernels on 16 streams 1,600 us against 1,618 with one window ahead, 7,000 kernels (24 levels) 498
 // against 520.  With fewer chains several workgroups cover for each other, and the registers of the
 // second window cost one of them: 8,192 kernels on 12 streams 500 us two ahead, 416 one ahead, 4,097 on 9
-// streams 758 and 670.
+// streams 758 and 670.  More than 32 levels and fixed nodes are one ahead everywhere, ahead of what they
+// replaced (30,001 candidates with slack: 9,216 kernels of 40 levels on 12 streams 833 -> 686 us, 10,000 of
+// 128 on 16 2,226 -> 2,007, 9 chains of 1,000 steps with fixed nodes 1,807 -> 768), 16 chains of 768 steps with
+// fixed nodes as before (1,848 and 1,885).
 template <bool SLACK, bool RAG>
 hipError_t launch_windowed_depth(const WinSlots &sl, const WinLaunch &l, const DevGraph &g, const DevChains &c,
                                  const WinArgs &a) {
