@@ -649,16 +649,18 @@ std::string jit_generate(const JitGraph &g, JitSlack slack) {
 // points <= est is exact, as in the interpreting kernel.  Energies and the idle term follow the
 // interpreting kernel's order, so both give bit-identical results.
 //
-// A step is a chain of three LDS reads (bucket, level byte, table entry), so what bounds the kernel is
-// their latency: waves per compute unit.  A 64 KB table leaves room for two workgroups, whatever their
-// size, so these take 512 or 1,024 candidates (jit_iv_block).  One kernel serves every size: it is compiled
-// for the largest (jit_iv_bound) and reads its size at run time, since a graph of 2,000 packs takes 50 s to
-// compile and a call with fewer candidates or other change points must not wait for that again.  The rows
-// in LDS hold each level times the table stride (up to 32 levels), invalid ones replaced when the rows
-// are copied, so a byte read is the table address and the step needs no clamp.  512 packs of 16 levels, 2^20 candidates: 16 intervals
-// 350 us with workgroups of 256 (8 waves a compute unit), 163 with 512 (16 waves); 64 intervals 741 and
-// 258 (one workgroup of 1,024).  The energy and finish times pass an asm every 4 steps: at 8 or 16 the
-// compiler takes more than 128 registers and half the waves (16 intervals: 297 and 316 us against 180).
+// A step is a chain of three LDS reads (bucket, level byte, table entry): with few waves a compute unit
+// their latency bounds the kernel, with 16 the VALU (0.73 of its peak on 512 packs) and the LDS (active 60
+// % of the time).  A 64 KB table leaves room for two workgroups, whatever their size, so these take 512 or
+// 1,024 candidates (jit_iv_block).  One kernel serves every size: it is compiled for the largest
+// (jit_iv_bound) and reads its size at run time, since a graph of 2,000 packs takes 50 s to compile and a
+// call with fewer candidates or other change points must not wait for that again.  The rows in LDS hold
+// each level times the table stride (up to 32 levels), invalid ones replaced when the rows are copied, so
+// a byte read is the table address and the step needs no clamp.  512 packs of 16 levels, 2^20 candidates:
+// 16 intervals 350 us with workgroups of 256 (8 waves a compute unit), 163 with 512 (16 waves); 64
+// intervals 741 and 191 (one workgroup of 1,024).  The energy and finish times pass an asm every 4 steps:
+// at 8 or 16 the compiler takes more than 128 registers and half the waves (16 intervals: 297 and 316 us
+// against 180).
 
 namespace {
 int iv_level_shift(const JitGraph &g) { return g.F <= 32 ? 3 : 0; }   // (31 * 8 fits a byte)
@@ -669,9 +671,10 @@ bool jit_iv_table_in_lds(const JitGraph &g) { return static_cast<size_t>(g.P) * 
 
 // 1,024 candidates leave a lane 128 registers, 512 256: that holds 49 finish times live at once in 121
 // registers and 124 in 171, while 69 spill 8 registers at 1,024.  A table in device memory has no copy to
-// share.
+// share, and around one of at most 16 KB workgroups of 256 already fill a compute unit (16 waves and more up
+// to 64 intervals).
 int jit_iv_bound(const JitGraph &g, int live) {
-    if (!jit_iv_table_in_lds(g)) return 256;
+    if (!jit_iv_table_in_lds(g) || static_cast<size_t>(g.P) * g.F * sizeof(float2) <= 16 * 1024) return 256;
     return live <= 64 ? 1024 : live <= 128 ? 512 : 256;
 }
 
@@ -679,7 +682,8 @@ std::string jit_generate_intervals(const JitGraph &g, int bound) {
     const bool tab_lds = jit_iv_table_in_lds(g);
     std::ostringstream o;
     o << "#define EMO_BLOCK " << bound << "\n" << (bound > 256 ? "#define EMO_GROUP ((int)blockDim.x)\n" : "") << kPrelude
-      << kEmoSelectSource << "\n";
+      << kEmoSelectSource << "\n#define EMO_BAD_DECL "
+      << (bound > 256 || !tab_lds ? "u8 *s_bad = (u8 *)(s_rows + EMO_GROUP * SD);\n" : "__shared__ u8 s_bad[EMO_BLOCK];\n");
     const long long ntab = static_cast<long long>(g.P) * g.F;
     o << "#define NTAB " << (ntab > 0 ? ntab : 1) << "\n";
     o << "#define EMO_F " << g.F << "\n";
@@ -791,10 +795,16 @@ struct EmoFwd { float T; float E; };
     // 2^18 against 47.  At 500 packs of 24 levels five are still ahead of four there (86 and 118).
     const char *const dev_waves = g.ops.size() <= 512 ? " __attribute__((amdgpu_waves_per_eu(1, 5)))"
                                                       : " __attribute__((amdgpu_waves_per_eu(1, 4)))";
-    // at 1,024 candidates four waves a SIMD, with all their registers: left to itself the compiler saves
-    // registers for waves that the LDS has no room for (512 packs: 47 registers and 45 us, with 98 40 us)
+    // At 1,024 candidates the compiler, left to itself, saves registers for eight waves a SIMD, which the LDS
+    // has no room for: held to four on graphs of more than 400 steps (512 packs of 16 levels, 2^18 candidates
+    // 40 us with 98 registers, 45 with 47; 900 of 8 64 us at 1,000 candidates, 79 left alone) and six on
+    // smaller ones, which need fewer registers and gain from the waves (300 of 8, 2^20 candidates, one
+    // interval 64 us with six, 87 with four; left alone 31 us at 1,000 candidates against 19).
+    const char *const lds_waves = bound < 1024          ? ""
+                                  : g.ops.size() > 400 ? " __attribute__((amdgpu_waves_per_eu(4, 4)))"
+                                                       : " __attribute__((amdgpu_waves_per_eu(4, 6)))";
     o << "extern \"C\" __global__ void __launch_bounds__(EMO_BLOCK)"
-      << (tab_lds ? (bound == 1024 ? " __attribute__((amdgpu_waves_per_eu(4, 4)))" : "") : dev_waves) << "\n"
+      << (tab_lds ? lds_waves : dev_waves) << "\n"
          "emo_iv(const u8 *__restrict__ lv, long long B, const float2 *__restrict__ tabg, EmoIvArgs a,\n"
          "    int copy, float inv_k, float *__restrict__ To, float *__restrict__ Eo, EmoTargets tg) {\n";
     if (tab_lds)
@@ -805,14 +815,16 @@ struct EmoFwd { float T; float E; };
     o << R"(  __shared__ float s_pts[256];
   __shared__ double s_dur[256];      // interval lengths T_{i+1} - T_i (T_0 = 0)
   __shared__ float s_idle[256];      // zero past F
-  // dynamic: the bucket table (M entries), then the group's rows, SD words a row, then a byte a row
-  // (it holds an invalid level)
+  // dynamic: the bucket table (M entries), then the group's rows, SD words a row, then s_bad: a byte a
+  // row (it holds an invalid level).  (Workgroups of 256 around a table in LDS have s_bad as a static array:
+  // 500 packs of 4 levels 36.9 us that way, 40.0 behind the rows; with a table in device memory it costs
+  // six registers there, and 900 packs of 24 levels the fourth wave.)
   extern __shared__ __align__(16) unsigned int emo_dyn[];
   const int K = a.K, M = a.M;
   const int SD = ((K + 3) >> 2) | 1;        // odd: a word column of the rows is conflict free
   int2 *s_bk = (int2 *)emo_dyn;
   unsigned int *s_rows = emo_dyn + 2 * M;
-  u8 *s_bad = (u8 *)(s_rows + EMO_GROUP * SD);
+  EMO_BAD_DECL
   const float scale = a.scale;
   s_bad[threadIdx.x] = 0;
   for (int i = threadIdx.x; i < K - 1; i += EMO_GROUP) s_pts[i] = a.pts[i];

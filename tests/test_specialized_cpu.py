@@ -212,13 +212,14 @@ def test_interval_kernels_compile(emo, hiprtc, tmp_path, k):
     notes, asm = check_code_object(path, ["emo_iv"])
 
 
-@pytest.mark.parametrize("kind, bound", [("training", 1024), ("chains-40", 1024), ("wide", 512), ("large-table", 256)])
+@pytest.mark.parametrize("kind, bound", [("training", 1024), ("chains-40", 1024), ("wide", 512), ("small-table", 256), ("large-table", 256)])
 def test_interval_kernel_of_every_bound(emo, hiprtc, tmp_path, kind, bound):
     """The time-interval kernel is compiled once, for the largest workgroup that its live finish times
-    leave enough registers for, and spills none there."""
-    g = {"training": lambda: synth.config_graph(3), "chains-40": lambda: synth.stream_graph(1, 400, 40, 4),
-         "wide": lambda: synth.random_dag(np.random.default_rng(1), 300, 0.03, 0.8, 8, shuffle_ids=False,
+    leave enough registers for and a table of more than 16 KB to share, and spills none there."""
+    g = {"training": lambda: synth.config_graph(3), "chains-40": lambda: synth.stream_graph(1, 400, 40, 8),
+         "wide": lambda: synth.random_dag(np.random.default_rng(1), 300, 0.03, 0.8, 16, shuffle_ids=False,
                                           shuffle_packs=False),
+         "small-table": lambda: synth.packed_graph(5, 500, 16, 4, sync_every=501),
          "large-table": lambda: synth.packed_graph(5, 600, 4, 24, sync_every=700)}[kind]()
     src = emo.EmoGraph(g, device=-1).interval_source()
     assert int(re.search(r"#define EMO_BLOCK (\d+)", src).group(1)) == bound
